@@ -2,6 +2,7 @@
 // host, workspace carving, and the launch sequence of each entry point.
 #include <prox.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -109,7 +110,8 @@ int stage2_launch_rows(int d, int wq, int batch) {
 // (scores == NULL: every channel).
 prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff,
                               const float *scores, uint8_t *mask, float *scores_copy, void *y,
-                              const Ws &W, Select sel, hipEvent_t *events, hipStream_t stream) {
+                              const Ws &W, Select sel, ScoreBracket br, hipEvent_t *events,
+                              hipStream_t stream) {
     const int d = m.d, f = m.f, dt = m.dtype;
     const uint16_t *xb = static_cast<const uint16_t *>(x);
     // With the threshold rule the kept count is found on the device: size the
@@ -130,7 +132,7 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
             const int list_mode = !scores ? kListNone : c0 == 0 ? kListWrite : kListRead;
             PROX_TRY(launch_stage2_mfma(dt, xb + (size_t)c0 * d, nb, d, f, m.s2, scores, k_ff,
                                         mask, c0 == 0 ? scores_copy : nullptr, W.sbuf, nwg,
-                                        c0 == 0 ? sel : Select{sel.tau_mode, sel.tau, nullptr},
+                                        c0 == 0 ? sel : Select{sel.tau_mode, sel.tau, nullptr}, br,
                                         m.act, W.klist, list_mode, stream));
             PROX_TRY(launch_stage2_down(dt, nb, d, f, m.s2.wd, W.sbuf, scores ? W.klist : nullptr,
                                         n_max, W.ypart + (size_t)c0 * d, ystride, stream));
@@ -147,7 +149,7 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
                                                     : kListRead;
         PROX_TRY(launch_stage2(dt, xb + (size_t)c0 * d, nb, d, f, m.s2, scores, k_ff, mask,
                                c0 == 0 ? scores_copy : nullptr, W.ypart + (size_t)c0 * d, ystride,
-                               nwg, c0 == 0 ? sel : Select{sel.tau_mode, sel.tau, nullptr}, m.act,
+                               nwg, c0 == 0 ? sel : Select{sel.tau_mode, sel.tau, nullptr}, br, m.act,
                                W.klist, list_mode, stream));
     }
     if (events) PROX_TRY(hipEventRecord(events[2], stream));
@@ -159,6 +161,29 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
 // Batch rows per matrix-core Stage-1 launch, or 0 for the dot-product kernel.
 int stage1_mfma_rows(int d, int qbits, int group, int batch, int k_in) {
     return qbits == 4 && batch >= proxy_mfma_min_rows(d) ? proxy_mfma_rows(d, group, k_in) : 0;
+}
+
+// The bracket of a top-k call's channel selection (ScoreBracket).  Its order
+// statistics go to the end of the kept-list area, [f - 2 n, f), which a call
+// that keeps k_ff <= f - 2 n channels never writes: the list takes [0, k_ff) and
+// f, and in a call without a list nothing.  NULL stats when there is no room,
+// d_ff is at most 4096 (with four scores per thread the radix passes are as
+// quick, and Stage 1 is spared its part: 23.2 against 23.9 us for the 1024 x
+// 3072 call), or k_ff is 0 (threshold mode).
+ScoreBracket score_bracket(int f, int k_ff, int32_t *klist) {
+    ScoreBracket br{};
+    const int T = proxy_tile(f), n = f / T;
+    if (k_ff < 1 || f <= 4 * kBlock || k_ff > f - 2 * n - 2) return br;
+    const double at = (double)k_ff * (T + 1) / (f + 1);   // expected rank in a tile, from 1
+    const int reach = T / 64;
+    br.r1 = std::min(std::max((int)at - reach, 1), T - 2 * reach - 1);
+    br.r2 = br.r1 + 2 * reach + 1;
+    const double half = 0.35 + 4 * 0.17 * T / std::sqrt((double)f);   // ranks
+    br.at = (float)((at - br.r1) / (br.r2 - br.r1));
+    br.half = (float)(half / (br.r2 - br.r1));
+    br.n = n;
+    br.stats = reinterpret_cast<uint32_t *>(klist + (f - 2 * n) / 2 * 2);   // 8-byte aligned
+    return br;
 }
 
 // The selection of each stage: counts (k_in, k_ff) or thresholds.
@@ -209,8 +234,10 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
     // reads the codes once for up to 16 rows; else the dot-product kernel.
     const int mfma_rows = stage1_mfma_rows(d, qbits, p->group, batch, k_in);
     const int pnb = mfma_rows ? mfma_rows : proxy_max_nb(d);
+    const ScoreBracket br = score_bracket(f, k_ff, W.klist);
     for (int c0 = 0; c0 < batch; c0 += pnb) {
         const int nb = batch - c0 < pnb ? batch - c0 : pnb;
+        const ScoreBracket out = c0 + pnb >= batch ? br : ScoreBracket{};
         const Select in_sel{rules.tau_mode, rules.tau_x, rules.counts};
         // With several matrix-core launches only the first selects; its list
         // of kept rows goes to the partial-y area, which Stage 2 writes only
@@ -219,16 +246,16 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
         if (mfma_rows)
             PROX_TRY(launch_proxy_mfma(dt, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
                                        c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel,
-                                       m.act, reinterpret_cast<int32_t *>(W.ypart), list_mode,
+                                       m.act, out, reinterpret_cast<int32_t *>(W.ypart), list_mode,
                                        stream));
         else
             PROX_TRY(launch_proxy(dt, qbits, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
                                   c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel, m.act,
-                                  stream));
+                                  out, stream));
     }
     if (events) PROX_TRY(hipEventRecord(events[1], stream));
     const Select ff_sel{rules.tau_mode, rules.tau_s, rules.counts ? rules.counts + 1 : nullptr};
-    return stage2_and_reduce(m, x, batch, k_ff, W.scores, mask, scores, y, W, ff_sel, events,
+    return stage2_and_reduce(m, x, batch, k_ff, W.scores, mask, scores, y, W, ff_sel, br, events,
                              stream);
 }
 
@@ -252,7 +279,7 @@ prox_status dense_impl(const Model &m, const void *x, int batch, void *y, void *
     if (ws_bytes < WsLayout(m.d, m.f, batch, m.s2.wq).total) return PROX_ERR_WORKSPACE;
     const Ws W = carve(ws, m.d, m.f, batch, m.s2.wq);
     return stage2_and_reduce(m, x, batch, m.f, nullptr, nullptr, nullptr, y, W,
-                             Select{0, 0.0f, nullptr}, nullptr, stream);
+                             Select{0, 0.0f, nullptr}, ScoreBracket{}, nullptr, stream);
 }
 
 }  // namespace

@@ -130,6 +130,23 @@ __device__ __forceinline__ uint2 load_stream8(const void *p) {
     return make_uint2(v.x, v.y);
 }
 
+// Bounds-checked loads from [p, p + bytes): past the end they return 0, at no
+// instruction's cost.  off: per lane, imm: a constant, both in bytes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ uint32_t buffer_load32(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
+    return __builtin_amdgcn_raw_buffer_load_b32(rs, off + (imm & 4095), imm & ~4095, 0);
+}
+__device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + (imm & 4095), imm & ~4095, 0);
+    return make_uint2(v[0], v[1]);
+}
+__device__ __forceinline__ uint4 buffer_load128(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + (imm & 4095), imm & ~4095, 0);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
 
 // Gate activation of the gated FFN: SiLU (act 0) or GELU z * Phi(z) (act 1),

@@ -34,12 +34,13 @@ hipError_t launch_unpack(int qbits, const void *blob, int d, int f, int group, i
 // Stage 1 for batch rows [row0, row0 + nb) of x_all (nb <= proxy_max_nb(d));
 // the input selection ranks all B_all rows (top k_in, or the threshold rule
 // of sel, for which k_in is the list capacity).  accumulate != 0 keeps
-// max(previous, new) scores.
+// max(previous, new) scores.  br.stats, given to a call's last launch: the order
+// statistics of every full tile's final scores go there.
 int proxy_max_nb(int d);
 hipError_t launch_proxy(int dtype, int qbits, const void *x_all, int B_all, int row0, int nb,
                         int d, int f, int group, int k_in, const void *blob,
                         uint8_t *in_mask, float *scores, int accumulate, Select sel, int act,
-                        hipStream_t stream);
+                        ScoreBracket br, hipStream_t stream);
 
 // Stage 1 on the matrix cores for INT4 proxies: batch rows [row0, row0 + nb)
 // with nb <= proxy_mfma_rows(d, group, k_in) (16, 8, or 0 when the kept-row
@@ -51,8 +52,8 @@ int proxy_mfma_rows(int d, int group, int k_in);
 // their list from it instead of selecting again.
 hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, int nb, int d,
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
-                             float *scores, int accumulate, Select sel, int act, int32_t *klist,
-                             int list_mode, hipStream_t stream);
+                             float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                             int32_t *klist, int list_mode, hipStream_t stream);
 // Batch rows from which Stage 1 uses the matrix cores: 3 up to d_model 4096,
 // 5 above (where its 2-byte code loads keep too few bytes in flight).
 inline int proxy_mfma_min_rows(int d) { return d <= 4096 ? 3 : 5; }
@@ -80,7 +81,7 @@ int stage2_rows(int d, int wq);
 enum KeptList { kListNone = 0, kListWrite = 1, kListRead = 2 };
 hipError_t launch_stage2(int dtype, const void *x, int nb, int d, int f, const Stage2Weights &w,
                          const float *scores, int k_ff, uint8_t *mask, float *scores_copy,
-                         float *ypart, int ystride, int nwg, Select sel, int act,
+                         float *ypart, int ystride, int nwg, Select sel, ScoreBracket br, int act,
                          int32_t *klist, int klist_mode, hipStream_t stream);
 // Stage 2 for up to kStage2MfmaRows batch rows (16-bit weights, d >= 4096:
 // stage2_mfma_ok) in two launches.  launch_stage2_mfma selects like
@@ -95,7 +96,7 @@ bool stage2_mfma_ok(int d, int wq);
 hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               const Stage2Weights &w, const float *scores, int k_ff,
                               uint8_t *mask, float *scores_copy, float *sbuf, int nwg, Select sel,
-                              int act, int32_t *klist, int klist_mode, hipStream_t stream);
+                              ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t stream);
 hipError_t launch_stage2_down(int dtype, int nb, int d, int f, const void *wd, const float *sbuf,
                               const int32_t *klist, int n_max, float *ypart, int ystride,
                               hipStream_t stream);

@@ -129,6 +129,23 @@ struct Select {
     int32_t *count;
 };
 
+// Where the k-th largest score should lie, from order statistics that Stage 1
+// leaves per full column tile (T scores each): the keys (fp32 bit patterns, close
+// to linear in the logarithm) of ranks r1 and r2 around the tile's share of
+// k_ff.  Their means over the n tiles, interpolated at the share, estimate the
+// k-th largest key; the bracket reaches `half` (in units of the gap) to each
+// side.  For scores spread alike over the tiles the estimate is off by about
+// 0.3 / T of the ranks (the means' curvature) and has a deviation of 0.17 /
+// sqrt(f) of them (simulated for products of Gaussians, alone and with
+// log-normal channel scales, f 3072 to 65536, k / f 0.02 to 0.95); the reach is
+// that offset plus four deviations, 0.7% of the channels at f = 28672.  A
+// bracket that misses costs one counting pass: the full search follows.
+struct ScoreBracket {
+    uint32_t *stats;   // [n][2], NULL: none
+    int n, r1, r2;
+    float at, half;
+};
+
 // ---------------------------------------------------------------------------
 // Workspace (no initialisation needed)
 // ---------------------------------------------------------------------------

@@ -57,7 +57,7 @@ template <int DT, int T, int C, int NX>
 __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
     const uint16_t *__restrict__ x_all, int B_all, int row0, int nb, int d, int f, int group,
     int k_in, const uint8_t *__restrict__ blob, uint8_t *__restrict__ in_mask,
-    float *__restrict__ scores, int accumulate, Select sel_rule, int act,
+    float *__restrict__ scores, int accumulate, Select sel_rule, int act, ScoreBracket br,
     int32_t *__restrict__ klist, int list_mode) {   // kept-row list of a multi-launch call
     static_assert(T == 64 || T == 128, "tile widths of the blob layout");
     static_assert(NX == 8 || NX == 16, "x rows kept in LDS");
@@ -363,6 +363,7 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
     // the up matrix in wave order, then |act(g~) u~|, then the max over the 16
     // rows inside each 16-lane row of the wave (lane % 16 = b, one column).
     const int b = tid % 16;
+    __shared__ uint32_t sc_tile[T];   // the tile's scores
 #pragma unroll
     for (int q = 0; q < T / 64; ++q) {
         const int col = tid / 16 + q * 64;
@@ -381,7 +382,17 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
         v = fmaxf(v, dpp_move<kDppRor4>(v));
         v = fmaxf(v, dpp_move<kDppRor8>(v));
         const int j = tile * T + col;
-        if (b == 0 && j < f) scores[j] = accumulate ? fmaxf(scores[j], v) : v;
+        if (b == 0) {
+            if (j < f) {
+                if (accumulate) v = fmaxf(scores[j], v);
+                scores[j] = v;
+            }
+            sc_tile[col] = __float_as_uint(v);
+        }
+    }
+    if (br.stats && (tile + 1) * T <= f) {
+        __syncthreads();
+        tile_order_stats<T>(sc_tile, br.r1, br.r2, br.stats + 2 * tile);
     }
 }
 
@@ -400,7 +411,7 @@ int proxy_mfma_rows(int d, int group, int k_in) {
 template <int DT, int T, int C, int NX>
 static hipError_t launch_mfma_t(const void *x_all, int B_all, int row0, int nb, int d, int f,
                                 int group, int k_in, const void *blob, uint8_t *in_mask,
-                                float *scores, int accumulate, Select sel, int act,
+                                float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                                 int32_t *klist, int list_mode, hipStream_t s) {
     const BlobLayout L(d, f, 4, group);
     const size_t lds = mfma_lds_bytes(k_in, d / group, NX);
@@ -410,17 +421,17 @@ static hipError_t launch_mfma_t(const void *x_all, int B_all, int row0, int nb, 
     if (e != hipSuccess) return e;
     proxy_mfma_kernel<DT, T, C, NX><<<L.n_tiles, kBlock, lds, s>>>(
         static_cast<const uint16_t *>(x_all), B_all, row0, nb, d, f, group, k_in,
-        static_cast<const uint8_t *>(blob), in_mask, scores, accumulate, sel, act, klist, list_mode);
+        static_cast<const uint8_t *>(blob), in_mask, scores, accumulate, sel, act, br, klist, list_mode);
     return hipGetLastError();
 }
 
 template <int DT, int T>
 static hipError_t launch_mfma_c(const void *x_all, int B_all, int row0, int nb, int d, int f,
                                 int group, int k_in, const void *blob, uint8_t *in_mask,
-                                float *scores, int accumulate, Select sel, int act,
+                                float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                                 int32_t *klist, int list_mode, hipStream_t s) {
     const int nx = proxy_mfma_rows(d, group, k_in);
-#define MF(C_, NX_) launch_mfma_t<DT, T, C_, NX_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, klist, list_mode, s)
+#define MF(C_, NX_) launch_mfma_t<DT, T, C_, NX_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
     if (d <= 4 * kBlock) return nx == 16 ? MF(4, 16) : MF(4, 8);
     if (d <= 8 * kBlock) return nx == 16 ? MF(8, 16) : MF(8, 8);
     return nx == 16 ? MF(16, 16) : MF(16, 8);
@@ -429,15 +440,15 @@ static hipError_t launch_mfma_c(const void *x_all, int B_all, int row0, int nb, 
 
 hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, int nb, int d,
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
-                             float *scores, int accumulate, Select sel, int act, int32_t *klist,
-                             int list_mode, hipStream_t s) {
+                             float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                             int32_t *klist, int list_mode, hipStream_t s) {
     if (nb < 1 || nb > proxy_mfma_rows(d, group, k_in)) return hipErrorInvalidValue;
     if (list_mode != kListNone && !klist) return hipErrorInvalidValue;
     if (proxy_tile(f) == 128)
-        return dtype == kBF16 ? launch_mfma_c<kBF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, klist, list_mode, s)
-                              : launch_mfma_c<kF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, klist, list_mode, s);
-    return dtype == kBF16 ? launch_mfma_c<kBF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, klist, list_mode, s)
-                          : launch_mfma_c<kF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, klist, list_mode, s);
+        return dtype == kBF16 ? launch_mfma_c<kBF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
+                              : launch_mfma_c<kF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
+    return dtype == kBF16 ? launch_mfma_c<kBF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
+                          : launch_mfma_c<kF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
 }
 
 }  // namespace prox

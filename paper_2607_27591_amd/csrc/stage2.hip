@@ -63,130 +63,213 @@ __host__ __device__ inline size_t stage2_head_bytes(int d, int nbt, int wq) {
     return xbytes > red ? xbytes : red;
 }
 
-// Score keys of one thread (item r = channel r * kBlock + base): the high
-// halves in registers, the complete key re-read from the scores
-// (L2-resident) when the high half ties.
 struct Stage2Smem {
     int list[kMaxSlice];
     float gu[kMaxSlice * kMaxParts * 2 * 2];   // [t][q][b][2] for nbt <= 2
 };
 
+// LDS of the selection prologue, besides the histogram.
+struct ChanSel {
+    SelScratch ss;
+    int cnt[kMaxBlockWaves], eq[kMaxBlockWaves];   // per-wave counts
+};
+
 // The selection prologue of both Stage 2 kernels: this workgroup's slice of the
 // kept channels (their ids to list[0..n), n returned, the slice's first
-// kept-list position to p0_out) and its chunk of the mask.
+// kept-list position to p0_out) and its share of the mask.
 // Every workgroup ranks the scores itself (top-k or the threshold rule), or,
 // for the later launches of a multi-launch batch, reads the first launch's list.
+// Bound by VALU issue (16 waves on 4 SIMDs: an instruction per score and thread
+// costs ~0.2 us at d_ff 28672) and by the latency of its barriers, while HBM
+// idles: so a score is compared a few times and counted by ballots, and only
+// the waves whose run of channels meets the slice look at single channels.
+// 8192 x 28672, one row, from the kernel's start to the first weight load: 7.4
+// us (loads back at 2.7, the bracket's pass 2.2, its scan 0.5, counts 0.7, slice
+// and x 1.2), against 8.6 with three radix passes over every score and a
+// (row, wave) table of ballots.
 // The caller synchronises before reading list.
 template <int C>
 __device__ __forceinline__ int stage2_slice(const float *__restrict__ scores, int f, int k_ff,
                                             uint8_t *__restrict__ mask,
                                             float *__restrict__ scores_copy, Select sel_rule,
-                                            int32_t *__restrict__ klist, int klist_mode,
-                                            uint32_t *hist, SelScratch &ss, TopKOrder<C> &ord,
-                                            int *list, int &p0_out) {
+                                            ScoreBracket br, int32_t *__restrict__ klist,
+                                            int klist_mode, uint32_t *hist, ChanSel &cs, int *list,
+                                            int &p0_out) {
     const int tid = threadIdx.x;
     const int nwg = gridDim.x, w = blockIdx.x;
     const bool sparse = scores != nullptr;
     // Channels of this workgroup: an even share of the n_ch kept channels
     // (with the threshold rule n_ch is only known after the selection).
     int n_ch = sparse ? k_ff : f;
-    int p0 = (int)((long long)w * n_ch / nwg), p1 = (int)((long long)(w + 1) * n_ch / nwg);
-    int n = p1 - p0;
+    int p0, p1;
+    auto split = [&](int n, int parts) {   // n parts < 2^25
+        p0 = (int)((uint32_t)(w * n) / (uint32_t)parts);
+        p1 = (int)((uint32_t)((w + 1) * n) / (uint32_t)parts);
+    };
+    // With the threshold rule the split is that of a launch for this count (the
+    // grid is sized for every channel; the workgroups past it get none), so the
+    // partial sums are those of the top-k launch with k = n_ch.
+    auto split_tau = [&]() {
+        const int nwg_k = min(nwg, stage2_wgs(n_ch));
+        if (w < nwg_k) split(n_ch, nwg_k);
+        else p0 = p1 = n_ch;
+    };
 
-
-    // ---- prologue: this workgroup's slice of the kept channels ----
     if (sparse && klist_mode == kListRead) {
         // A launch for the same call already selected: its list gives the
         // same slice as ranking again would.
         n_ch = klist[f];
-        if (sel_rule.tau_mode) {
-            const int nwg_k = min(nwg, stage2_wgs(n_ch));
-            p0 = w < nwg_k ? (int)((long long)w * n_ch / nwg_k) : n_ch;
-            p1 = w < nwg_k ? (int)((long long)(w + 1) * n_ch / nwg_k) : n_ch;
-            n = p1 - p0;
-        }
-        for (int t = tid; t < n; t += kBlock) list[t] = klist[p0 + t];
+        if (sel_rule.tau_mode) split_tau();
+        else split(n_ch, nwg);
+        for (int t = tid; t < p1 - p0; t += kBlock) list[t] = klist[p0 + t];
         __syncthreads();
     } else if (sparse) {
-        // Item r of thread t is channel r * kBlock + t (coalesced loads).
+        const int lane = lane_id(), wid = wave_id();
+        const int first = wid * C * kWave + lane;   // channel of item 0
         // Scores are |s~| >= 0, so their IEEE bit patterns order like the
-        // values; channels past f get key 0.
+        // values.  Loads past f return 0 (bounds-checked buffer loads).
         uint32_t key[C];
+        const auto rs = buffer_of(scores, (uint32_t)f * 4);
 #pragma unroll
-        for (int r = 0; r < C; ++r) {
-            key[r] = r * kBlock + tid < f ? __float_as_uint(scores[r * kBlock + tid]) : 0u;
-        }
-        uint64_t sel = 0;
+        for (int r = 0; r < C; ++r) key[r] = buffer_load32(rs, first * 4, r * kWave * 4);
+        uint32_t v = 0, top = 0x7FFFFFFFu;   // kept: v <= key <= top, when `plain`
+        int need = 0, bucket = 0;
         if (sel_rule.tau_mode) {
-            // Threshold rule: keep channel j when score_j >= tau_s.
-#pragma unroll
-            for (int r = 0; r < C; ++r)
-                sel |= (uint64_t)(r * kBlock + tid < f && __uint_as_float(key[r]) >= sel_rule.tau) << r;
-            topk_order<kBlock, C>(sel, ord);
-            n_ch = topk_selected_before<kBlock, C>(ord, C * kBlock);
-            // Split over the workgroups a launch for this count would have
-            // (the grid is sized for every channel; the rest get none), so
-            // the partial sums are those of the top-k launch with k = n_ch.
-            const int nwg_k = min(nwg, stage2_wgs(n_ch));
-            p0 = w < nwg_k ? (int)((long long)w * n_ch / nwg_k) : n_ch;
-            p1 = w < nwg_k ? (int)((long long)(w + 1) * n_ch / nwg_k) : n_ch;
-            n = p1 - p0;
-            if (w == 0 && tid == 0 && sel_rule.count) *sel_rule.count = n_ch;
+            // score >= tau as bit patterns, for tau > 0 (top: no NaN).
+            if (sel_rule.tau > 0.0f) v = __float_as_uint(sel_rule.tau);
+            top = 0x7F800000u;
         } else {
-            topk_select_f32<kBlock, C>(key, f, k_ff, hist, ss, ord);
-        }
-        // This workgroup's slice of positions straight from the order tables.
-        // The (row, wave) entry holding position p0 is found by one thread;
-        // then wave v expands entries e0 + v, e0 + v + 16, ... lane by lane
-        // (lane l: bit l of the entry's ballot, its position by a lane count)
-        // until the entries pass p1.
-        if (n > 0) {
-            if (tid < C * kMaxBlockWaves) {
-                const int pos = ord.off[tid];
-                const int cnt = __popcll(ord.sel[tid / kMaxBlockWaves][tid % kMaxBlockWaves]);
-                if (pos <= p0 && p0 < pos + cnt) ss.pick[0] = tid;   // exactly one entry
+            bool done = false;
+            if (br.stats) {
+                // Every wave works out the bracket alike, all loads in flight.
+                constexpr int NS = C <= 16 ? 4 : 8;   // tiles per lane: T is 64 up to d_ff 24448
+                uint2 e[NS];
+                const auto bs = buffer_of(br.stats, (uint32_t)br.n * 8);
+#pragma unroll
+                for (int t = 0; t < NS; ++t) e[t] = buffer_load64(bs, lane * 8, t * kWave * 8);
+                if (tid < kBracketBins<C> / 4) reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
+                split(n_ch, nwg);
+                float s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+                for (int t = 0; t < NS; ++t) {
+                    s1 += (float)e[t].x;
+                    s2 += (float)e[t].y;
+                }
+                const float inv = 1.0f / (float)br.n;
+                s1 = wave_sum(s1) * inv;
+                s2 = wave_sum(s2) * inv;
+                const float gap = s1 - s2;   // >= 0
+                const float hi = s1 - gap * (br.at - br.half), lo = s1 - gap * (br.at + br.half);
+                __syncthreads();   // the zeroed histogram
+                if (lo >= 1.0f && hi < 2147483000.0f)
+                    done = kth_score_bracket<C>(key, k_ff, (uint32_t)lo, (uint32_t)hi + 1u, hist,
+                                                cs.ss, cs.cnt, v, need, bucket);
+            } else {
+                split(n_ch, nwg);
             }
-            __syncthreads();
-            const int wid = wave_id(), lane = lane_id();
-            for (int e = ss.pick[0] + wid; e < C * kMaxBlockWaves; e += kMaxBlockWaves) {
-                const int pos = ord.off[e];   // wave-uniform
-                if (pos >= p1) break;
-                const uint64_t m = ord.sel[e / kMaxBlockWaves][e % kMaxBlockWaves];
-                const int q = pos + (int)lanes_below(m);
-                if (((m >> lane) & 1) && q >= p0 && q < p1) {
-                    const int j = min((e / kMaxBlockWaves) * kBlock + (e % kMaxBlockWaves) * kWave + lane,
-                                      f - 1);   // rows in bounds
-                    list[q - p0] = j;
-                    if (klist_mode == kListWrite) klist[q] = j;
+            if (!done) kth_score<C>(key, f, first, k_ff, hist, cs.ss, v, need, bucket);
+        }
+        // Selected: v <= key <= top, but for v = 0 (keys past f are 0 too) and for
+        // a k-th key of which only `need` equal ones, in index order, are in.
+        const bool tie = need < bucket, plain = v != 0 && !tie;
+        const uint32_t span = top - v;
+        auto over = [&](int r) {
+            if (sel_rule.tau_mode) return first + r * kWave < f && __uint_as_float(key[r]) >= sel_rule.tau;
+            return tie ? key[r] > v : first + r * kWave < f;
+        };
+        auto equal = [&](int r) { return key[r] == v && first + r * kWave < f; };
+        int n_over = 0, n_equal = 0;
+        if (plain) {
+#pragma unroll
+            for (int r = 0; r < C; ++r) n_over += __popcll(__ballot(key[r] - v <= span));
+        } else {
+#pragma unroll
+            for (int r = 0; r < C; ++r) {
+                n_over += __popcll(__ballot(over(r)));
+                n_equal += tie ? __popcll(__ballot(equal(r))) : 0;
+            }
+        }
+        if (lane == 0) {
+            cs.cnt[wid] = n_over;
+            cs.eq[wid] = n_equal;
+        }
+        __syncthreads();
+        // Counts of the waves before this one, and in all.
+        const int ca = wave_inclusive_scan(lane < kMaxBlockWaves ? cs.cnt[lane] : 0);
+        int base = wid > 0 ? __builtin_amdgcn_readlane(ca, wid - 1) : 0, n_sel = n_over, eq_run = 0;
+        if (tie) {
+            const int ce = wave_inclusive_scan(lane < kMaxBlockWaves ? cs.eq[lane] : 0);
+            eq_run = wid > 0 ? __builtin_amdgcn_readlane(ce, wid - 1) : 0;
+            base += min(need, eq_run);
+            n_sel += min(need, eq_run + n_equal) - min(need, eq_run);
+        }
+        if (sel_rule.tau_mode) {
+            n_ch = __builtin_amdgcn_readlane(ca, kMaxBlockWaves - 1);
+            split_tau();
+            if (w == 0 && tid == 0 && sel_rule.count) *sel_rule.count = n_ch;
+        }
+        // The waves that hold a part of the slice write it to the list; of the
+        // mask's (wave, row) entries, w, w + nwg, ... are this workgroup's.
+        const bool in_slice = p0 < p1 && base < p1 && base + n_sel > p0;   // wave-uniform
+        const int m0 = (int)((uint32_t)(w + nwg - (int)((uint32_t)(wid * C) % (uint32_t)nwg)) % (uint32_t)nwg);
+        if (in_slice || m0 < C) {
+            uint32_t lo = 0, hi = 0;   // lane r: the ballot of row r's selected channels
+            if (plain) {
+#pragma unroll
+                for (int r = 0; r < C; ++r) {
+                    const uint64_t m = __ballot(key[r] - v <= span);
+                    lo = write_lane(lo, (uint32_t)m, r);
+                    hi = write_lane(hi, (uint32_t)(m >> 32), r);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < C; ++r) {
+                    uint64_t m = __ballot(over(r));
+                    if (tie) {
+                        const uint64_t e = __ballot(equal(r));
+                        m |= __ballot(((e >> lane) & 1) && eq_run + (int)lanes_below(e) < need);
+                        eq_run += __popcll(e);
+                    }
+                    lo = write_lane(lo, (uint32_t)m, r);
+                    hi = write_lane(hi, (uint32_t)(m >> 32), r);
+                }
+            }
+            auto ballot_of = [&](int r) {
+                return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, r) << 32) |
+                       (uint32_t)__builtin_amdgcn_readlane((int)lo, r);
+            };
+            if (in_slice) {
+                const int cnt = __popc(lo) + __popc(hi);
+                const int pos = base + wave_inclusive_scan(cnt) - cnt;
+                uint64_t hit = __ballot(cnt > 0 && pos < p1 && pos + cnt > p0);
+                while (hit) {
+                    const int r = __builtin_ctzll(hit);
+                    hit &= hit - 1;
+                    const uint64_t m = ballot_of(r);
+                    const int q = __builtin_amdgcn_readlane(pos, r) + (int)lanes_below(m);
+                    if (((m >> lane) & 1) && q >= p0 && q < p1) {
+                        const int j = min(first + r * kWave, f - 1);   // rows in bounds
+                        list[q - p0] = j;
+                        if (klist_mode == kListWrite) klist[q] = j;
+                    }
+                }
+            }
+            for (int r = m0; r < C; r += nwg) {
+                const uint64_t m = ballot_of(r);
+                const int j = first + r * kWave;
+                if (j < f) {
+                    mask[j] = (uint8_t)((m >> lane) & 1);
+                    if (scores_copy) scores_copy[j] = scores[j];
                 }
             }
         }
         if (klist_mode == kListWrite && w == 0 && tid == 0) klist[f] = n_ch;
-        (void)sel;
-        __syncthreads();
     } else {
-        for (int t = tid; t < n; t += kBlock) list[t] = p0 + t;
+        split(n_ch, nwg);
+        for (int t = tid; t < p1 - p0; t += kBlock) list[t] = p0 + t;
     }
     p0_out = p0;
-    return n;
-}
-
-// This workgroup's chunk of the channel mask (and of the score copy) from
-// the order tables of a launch that selected.  Called after the prologue's
-// last barrier, so the stores overlap the weight stream instead of holding a
-// barrier until they are acknowledged.
-template <int C>
-__device__ __forceinline__ void stage2_mask_chunk(const TopKOrder<C> &ord, const float *scores,
-                                                  int f, uint8_t *mask, float *scores_copy,
-                                                  int klist_mode) {
-    if (!scores || klist_mode == kListRead) return;
-    const int nwg = gridDim.x, w = blockIdx.x;
-    const int mchunk = (f + nwg - 1) / nwg;   // mask entries written by this workgroup
-    const int m_lo = w * mchunk, m_hi = min(m_lo + mchunk, f);
-    for (int i = m_lo + (int)threadIdx.x; i < m_hi; i += kBlock) {
-        mask[i] = topk_is_selected<kBlock, C>(ord, i) ? 1 : 0;
-        if (scores_copy) scores_copy[i] = scores[i];
-    }
+    return p1 - p0;
 }
 
 // WQ: 16 for 16-bit weights, 4 for INT4 codes (wt.sg/su/sd: their scales).
@@ -196,7 +279,7 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
     const float *__restrict__ scores,   // NULL: dense FFN over all f channels
     int k_ff, uint8_t *__restrict__ mask, float *__restrict__ scores_copy,
     float *__restrict__ ypart, int ypart_stride,   // partial y rows per workgroup
-    Select sel_rule, int act,                       // act: gate activation
+    Select sel_rule, ScoreBracket br, int act,      // act: gate activation
     int32_t *__restrict__ klist, int klist_mode) {  // kept-channel list, KeptList mode
     static_assert(WQ == 16 || WQ == 4, "16-bit or INT4 weights");
     const uint16_t *__restrict__ wg = static_cast<const uint16_t *>(wt.wg);
@@ -204,8 +287,7 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
     const uint16_t *__restrict__ wd = static_cast<const uint16_t *>(wt.wd);
     const int tid = threadIdx.x, wid = tid / kWave, lane = lane_id();
 
-    __shared__ SelScratch ss;
-    __shared__ TopKOrder<C> ord;
+    __shared__ ChanSel cs;
     __shared__ Stage2Smem sm;
     // The channel selection's histogram, then x [NB][d] or the down reduction
     // | s [slice][NB].
@@ -215,7 +297,7 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
     // latency hides behind the ranking, and stored once the selection's
     // histogram is dead; with 64 score rows per thread the registers are
     // short, and x is loaded after it.  Thread t holds uint4 number
-    // k * kBlock + t of the [NB][d / 8] vectors.
+    // k * kBlock + t of the [NB][d / 8] vectors (rows past nb: zeros).
     const bool xl = x_in_lds(d, NB);   // always true with INT4 weights (host-checked)
     const int nvec = d / 8;
     constexpr int XPT = NB * kMaxDModel / 8 / kBlock < 4 ? NB * kMaxDModel / 8 / kBlock : 4;
@@ -224,20 +306,15 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
     constexpr bool kEarlyX = C <= 32;
     uint4 xr[XPT];
     auto load_x = [&]() {
+        const auto rs = buffer_of(x, xl ? (uint32_t)(nb * d) * 2 : 0u);
 #pragma unroll
-        for (int k = 0; k < XPT; ++k) {
-            const int e = k * kBlock + tid, b = e / nvec;
-            xr[k] = xl && e < NB * nvec && b < nb
-                        ? reinterpret_cast<const uint4 *>(x + (size_t)b * d)[e % nvec]
-                        : make_uint4(0, 0, 0, 0);
-        }
+        for (int k = 0; k < XPT; ++k) xr[k] = buffer_load128(rs, tid * 16, k * kBlock * 16);
     };
     if constexpr (kEarlyX) load_x();
 
     int p0;
-    const int n = stage2_slice<C>(scores, f, k_ff, mask, scores_copy, sel_rule, klist,
-                                  klist_mode, reinterpret_cast<uint32_t *>(dyn), ss, ord,
-                                  sm.list, p0);
+    const int n = stage2_slice<C>(scores, f, k_ff, mask, scores_copy, sel_rule, br, klist,
+                                  klist_mode, reinterpret_cast<uint32_t *>(dyn), cs, sm.list, p0);
     (void)p0;
     if constexpr (!kEarlyX) load_x();
 
@@ -280,7 +357,6 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
         }
     }
     __syncthreads();
-    stage2_mask_chunk<C>(ord, scores, f, mask, scores_copy, klist_mode);
 
     // ---- gate/up: units (channel t, part q) over the 16 waves ----
     const int Q = gateup_parts(d, NB, WQ);
@@ -775,26 +851,23 @@ template <int DT, int C>
 __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
     const uint16_t *__restrict__ x, int nb, int d, int f, Stage2Weights wt,
     const float *__restrict__ scores, int k_ff, uint8_t *__restrict__ mask,
-    float *__restrict__ scores_copy, float *__restrict__ sbuf, Select sel_rule, int act,
-    int32_t *__restrict__ klist, int klist_mode) {
+    float *__restrict__ scores_copy, float *__restrict__ sbuf, Select sel_rule, ScoreBracket br,
+    int act, int32_t *__restrict__ klist, int klist_mode) {
     constexpr int R = kStage2MfmaRows;
     const uint16_t *__restrict__ wg = static_cast<const uint16_t *>(wt.wg);
     const uint16_t *__restrict__ wu = static_cast<const uint16_t *>(wt.wu);
     const int tid = threadIdx.x, wid = tid / kWave, lane = lane_id();
 
-    __shared__ SelScratch ss;
-    __shared__ TopKOrder<C> ord;
+    __shared__ ChanSel cs;
     __shared__ int list[kMaxSlice];
     // The channel selection's histogram, then red [tiles][2][waves][lanes] float4.
     extern __shared__ __align__(16) float dyn[];
     float4 *red = reinterpret_cast<float4 *>(dyn);
 
     int p0;
-    const int n = stage2_slice<C>(scores, f, k_ff, mask, scores_copy, sel_rule, klist,
-                                  klist_mode, reinterpret_cast<uint32_t *>(dyn), ss, ord, list,
-                                  p0);
+    const int n = stage2_slice<C>(scores, f, k_ff, mask, scores_copy, sel_rule, br, klist,
+                                  klist_mode, reinterpret_cast<uint32_t *>(dyn), cs, list, p0);
     __syncthreads();
-    stage2_mask_chunk<C>(ord, scores, f, mask, scores_copy, klist_mode);
 
     // ---- gate/up ----
     const int nsteps = d / 32;   // steps of 32 inputs
@@ -1058,7 +1131,7 @@ static hipError_t allow_lds(K kernel, size_t bytes) {
 template <int NB, int DT, int C, int WQ>
 static hipError_t launch_stage2_t(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                   const float *scores, int k_ff, uint8_t *mask, float *scores_copy,
-                                  float *ypart, int ystride, int nwg, Select sel_rule, int act,
+                                  float *ypart, int ystride, int nwg, Select sel_rule, ScoreBracket br, int act,
                                   int32_t *klist, int klist_mode, hipStream_t st) {
     if (WQ == 4 && !x_in_lds(d, NB)) return hipErrorInvalidValue;
     const size_t lds = stage2_lds_bytes(d, NB, WQ, scores != nullptr);
@@ -1066,17 +1139,17 @@ static hipError_t launch_stage2_t(const void *x, int nb, int d, int f, const Sta
     if (e != hipSuccess) return e;
     stage2_kernel<NB, DT, C, WQ><<<nwg, kBlock, lds, st>>>(
         static_cast<const uint16_t *>(x), nb, d, f, wt, scores, k_ff, mask, scores_copy, ypart,
-        ystride, sel_rule, act, klist, klist_mode);
+        ystride, sel_rule, br, act, klist, klist_mode);
     return hipGetLastError();
 }
 
 template <int NB, int DT, int WQ>
 static hipError_t launch_stage2_c(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                   const float *scores, int k_ff, uint8_t *mask, float *scores_copy,
-                                  float *ypart, int ystride, int nwg, Select sel_rule, int act,
+                                  float *ypart, int ystride, int nwg, Select sel_rule, ScoreBracket br, int act,
                                   int32_t *klist, int klist_mode, hipStream_t st) {
     // C = score rows per thread of the channel top-k (the dense path has none).
-#define S2C(C_) launch_stage2_t<NB, DT, C_, WQ>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, ypart, ystride, nwg, sel_rule, act, klist, klist_mode, st)
+#define S2C(C_) launch_stage2_t<NB, DT, C_, WQ>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, ypart, ystride, nwg, sel_rule, br, act, klist, klist_mode, st)
     // As few score rows per thread as d_ff needs (below 16 not for eight rows
     // of INT4 weights, whose registers are full).
     if constexpr (WQ == 16 || NB <= 4) {
@@ -1093,11 +1166,11 @@ static hipError_t launch_stage2_c(const void *x, int nb, int d, int f, const Sta
 
 hipError_t launch_stage2(int dtype, const void *x, int nb, int d, int f, const Stage2Weights &wt,
                          const float *scores, int k_ff, uint8_t *mask, float *scores_copy,
-                         float *ypart, int ystride, int nwg, Select sel_rule, int act,
-                         int32_t *klist, int klist_mode, hipStream_t st) {
+                         float *ypart, int ystride, int nwg, Select sel_rule, ScoreBracket br,
+                         int act, int32_t *klist, int klist_mode, hipStream_t st) {
     if (nb < 1 || nb > stage2_rows(d, wt.wq)) return hipErrorInvalidValue;
     if (klist_mode != kListNone && (!scores || !klist)) return hipErrorInvalidValue;
-#define S2(NB_, DT_, WQ_) return launch_stage2_c<NB_, DT_, WQ_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, ypart, ystride, nwg, sel_rule, act, klist, klist_mode, st)
+#define S2(NB_, DT_, WQ_) return launch_stage2_c<NB_, DT_, WQ_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, ypart, ystride, nwg, sel_rule, br, act, klist, klist_mode, st)
 #define S2NB(DT_, WQ_)                   \
     switch (stage2_nb_t(nb)) {           \
         case 1: S2(1, DT_, WQ_);         \
@@ -1119,13 +1192,13 @@ template <int DT, int C>
 static hipError_t launch_stage2m_t(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
-                                   int act, int32_t *klist, int klist_mode, hipStream_t st) {
+                                   ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
     const size_t lds = stage2_mfma_lds_bytes();
     hipError_t e = allow_lds(stage2_mfma_kernel<DT, C>, lds);
     if (e != hipSuccess) return e;
     stage2_mfma_kernel<DT, C><<<nwg, kBlock, lds, st>>>(
         static_cast<const uint16_t *>(x), nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf,
-        sel_rule, act, klist, klist_mode);
+        sel_rule, br, act, klist, klist_mode);
     return hipGetLastError();
 }
 
@@ -1133,8 +1206,8 @@ template <int DT>
 static hipError_t launch_stage2m_c(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
-                                   int act, int32_t *klist, int klist_mode, hipStream_t st) {
-#define S2M(C_) launch_stage2m_t<DT, C_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, act, klist, klist_mode, st)
+                                   ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
+#define S2M(C_) launch_stage2m_t<DT, C_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
     if (scores && f <= 4 * kBlock) return S2M(4);
     if (scores && f <= 8 * kBlock) return S2M(8);
     if (scores && f <= 12 * kBlock) return S2M(12);
@@ -1148,8 +1221,8 @@ static hipError_t launch_stage2m_c(const void *x, int nb, int d, int f, const St
 hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               const Stage2Weights &wt, const float *scores, int k_ff,
                               uint8_t *mask, float *scores_copy, float *sbuf, int nwg,
-                              Select sel_rule, int act, int32_t *klist, int klist_mode,
-                              hipStream_t st) {
+                              Select sel_rule, ScoreBracket br, int act, int32_t *klist,
+                              int klist_mode, hipStream_t st) {
     const int n_ch = scores && !sel_rule.tau_mode ? k_ff : f;   // the kept-list length
     if (nb < 1 || nb > kStage2MfmaRows || !stage2_mfma_ok(d, wt.wq) || nwg < 1 ||
         nwg > kStage2MaxWGs || (long long)n_ch > (long long)kMaxSlice * nwg || !sbuf)
@@ -1159,9 +1232,9 @@ hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
         return hipErrorInvalidValue;
     if (dtype == kBF16)
         return launch_stage2m_c<kBF16>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf,
-                                       nwg, sel_rule, act, klist, klist_mode, st);
+                                       nwg, sel_rule, br, act, klist, klist_mode, st);
     return launch_stage2m_c<kF16>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg,
-                                  sel_rule, act, klist, klist_mode, st);
+                                  sel_rule, br, act, klist, klist_mode, st);
 }
 
 hipError_t launch_stage2_down(int dtype, int nb, int d, int f, const void *wd, const float *sbuf,

@@ -1,18 +1,17 @@
 // Block-wide exact top-k, used in the prologues of the Stage 1 and Stage 2
 // kernels (App. A.6 per-token top-k rule, ties to the lower index).
 //
-// Items are owned strided: item r of thread t is index r * NT + t, so every
-// key load is coalesced, and a wave's ballot over item r covers 64
-// consecutive indices.  Keys are unsigned and order like the values they
-// stand for: 15-bit magnitude patterns of 16-bit floats (input selection) or
-// bit patterns of non-negative fp32 scores (channel selection).  Items past
-// n hold key 0.
+// Input selection: items are owned strided, item r of thread t is index
+// r * NT + t, so every key load is coalesced, and a wave's ballot over item r
+// covers 64 consecutive indices.  Keys are unsigned and order like the values
+// they stand for: 15-bit magnitude patterns of 16-bit floats (input selection)
+// or bit patterns of non-negative fp32 scores (channel selection, whose
+// ownership is described with it).  Items past n hold key 0.
 //
 // The k-th largest key is found with histograms in LDS: one pass over all
 // 2^15 values of a 16-bit magnitude (two 16-bit counters per word), or, for
-// fp32 scores, three passes over 12 + 11 + 8 bits (11 + 11 + 9 up to 16 keys
-// per thread), the later ones over the keys that match the digits found so
-// far, ending as soon as the found bin is wholly in the top k.  Small blocks
+// fp32 scores, from a bracket that Stage 1 leaves (kth_score_bracket), else in
+// three radix passes (kth_score).  Small blocks
 // of 16-bit keys (at most 4096 items) take two passes of 12 + 3 bits instead,
 // whose scans are cheaper than the items they add.  A pass is one round of
 // LDS atomics and a block-wide scan of the bin counts from the top.  Ties at the k-th key are
@@ -50,9 +49,10 @@ __host__ __device__ constexpr uint32_t hist_pad(uint32_t w) { return w + (w >> 4
 constexpr int kSelPadWords = 16384 + 1024;
 
 // LDS words of the histograms: 2^15 packed 16-bit counters (input keys), or
-// at most 2^12 + 2^11 + 2^8 counters (the three digits of a score key).
+// for score keys two of 2^12 counters (a bracket's passes; the three digits
+// of a whole score key take at most 2^12 + 2^11 + 2^8).
 constexpr int kSelHistU16Words = kSelPadWords;
-constexpr int kSelHistF32Words = 4096 + 2048 + 256;
+constexpr int kSelHistF32Words = 2 * 4096;
 constexpr size_t kSelHistU16Bytes = (size_t)kSelHistU16Words * 4;
 constexpr size_t kSelHistF32Bytes = (size_t)kSelHistF32Words * 4;
 
@@ -298,18 +298,18 @@ __device__ __forceinline__ void topk_table_cut(const uint32_t (&key)[C], int n, 
 
 // One narrow digit pass: counts bits [shift, shift + log2 NBINS) of the keys
 // whose higher bits equal `prefix` (bits from `shift + log2 NBINS` up), into
-// h (NBINS words, zero), then finds the bin holding the kk-th largest.
-template <int NT, int C, int NBINS>
-__device__ __forceinline__ void narrow_pass(const uint32_t (&key)[C], int n, int shift,
-                                            uint32_t prefix, uint32_t *h, SelScratch &ss,
+// h (NBINS words, zero), then finds the bin holding the kk-th largest.  Item r
+// of this thread has index first + r * stride.
+template <int C, int NBINS>
+__device__ __forceinline__ void narrow_pass(const uint32_t (&key)[C], int n, int first, int stride,
+                                            int shift, uint32_t prefix, uint32_t *h, SelScratch &ss,
                                             int &kk, int &bucket, uint32_t &digit) {
-    const int tid = threadIdx.x;
     constexpr uint32_t kMaskBins = NBINS - 1;
     const int top = shift + __builtin_ctz(NBINS);   // bits at or above top: the prefix
 #pragma unroll
     for (int r = 0; r < C; ++r) {
         // Keys past n are 0: masked whenever the prefix admits 0.
-        const bool match = (top >= 32 || (key[r] >> top) == prefix) && (prefix != 0 || r * NT + tid < n);
+        const bool match = (top >= 32 || (key[r] >> top) == prefix) && (prefix != 0 || first + r * stride < n);
         if (match) atomicAdd(&h[(key[r] >> shift) & kMaskBins], 1u);
     }
     __syncthreads();
@@ -335,10 +335,10 @@ __device__ __forceinline__ void topk_select_u15(const uint32_t (&key)[C], int n,
         __syncthreads();
         int kk = k, bucket;
         uint32_t d1, d2;
-        narrow_pass<NT, C, 4096>(key, n, 3, 0, h1, ss, kk, bucket, d1);
+        narrow_pass<C, 4096>(key, n, tid, NT, 3, 0, h1, ss, kk, bucket, d1);
         uint32_t v = d1 << 3;
         if (kk < bucket) {
-            narrow_pass<NT, C, 8>(key, n, 0, d1, h2, ss, kk, bucket, d2);
+            narrow_pass<C, 8>(key, n, tid, NT, 0, d1, h2, ss, kk, bucket, d2);
             v = (d1 << 3) | d2;
             if (kk < bucket) {
                 topk_table_cut<NT, C>(key, n, v, kk, hist, ord);
@@ -362,42 +362,127 @@ __device__ __forceinline__ void topk_select_u15(const uint32_t (&key)[C], int n,
     else topk_table<NT, C>(key, n, v, ord);
 }
 
-// Top k (1 <= k <= n) of non-negative fp32 keys (bit 31 clear) in three
+// ---------------------------------------------------------------------------
+// Channel selection of Stage 2 (non-negative fp32 scores, bit 31 clear)
+// ---------------------------------------------------------------------------
+// Each wave owns a run of C * 64 consecutive channels: item r of lane l of
+// wave w is channel (w * C + r) * 64 + l, so a wave's kept channels are one
+// run of positions and 16 wave counts give every position.
+
+// The k-th largest key v, of whose `bucket` equal keys `need` are in, by three
 // radix passes over small histograms: bits 30..20, 19..9 and 8..0 (2048, 2048
 // and 512 bins) up to 16 keys per thread, else bits 30..19, 18..8 and 7..0
-// (4096, 2048 and 256 bins); the later passes count only the keys matching
-// the digits found so far, and stop once the found bin is wholly in the top
-// k.  Ties at the k-th key are cut by index.  hist: kSelHistF32Words words of
-// LDS.  Fills ord.
-template <int NT, int C>
-__device__ __forceinline__ void topk_select_f32(const uint32_t (&key)[C], int n, int k,
-                                                uint32_t *hist, SelScratch &ss,
-                                                TopKOrder<C> &ord) {
+// (4096, 2048 and 256 bins); the later passes count only the keys matching the
+// digits found so far, and stop once the found bin is wholly in the top k
+// (then v is the bin's lower edge and need = bucket).
+// hist: kSelHistF32Words words of LDS.
+template <int C>
+__device__ __forceinline__ void kth_score(const uint32_t (&key)[C], int n, int first, int k,
+                                          uint32_t *hist, SelScratch &ss, uint32_t &v, int &need,
+                                          int &bucket) {
     const int tid = threadIdx.x;
-    constexpr int L1 = C * NT <= 16384 ? 11 : 12, L2 = 11, L3 = 31 - L1 - L2;
+    constexpr int L1 = C * kBlock <= 16384 ? 11 : 12, L2 = 11, L3 = 31 - L1 - L2;
     constexpr int S1 = 31 - L1, S2 = S1 - L2;
     static_assert((1 << L1) + (1 << L2) + (1 << L3) <= kSelHistF32Words, "histograms fit");
     uint32_t *g1 = hist, *g2 = hist + (1 << L1), *g3 = g2 + (1 << L2);
-    for (int i = tid; i < ((1 << L1) + (1 << L2) + (1 << L3)) / 4; i += NT)
+    __syncthreads();   // an earlier search may still read hist
+    for (int i = tid; i < ((1 << L1) + (1 << L2) + (1 << L3)) / 4; i += kBlock)
         reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    int kk = k, bucket;
     uint32_t d1, d2, d3;
-    narrow_pass<NT, C, (1 << L1)>(key, n, S1, 0, g1, ss, kk, bucket, d1);
-    uint32_t v = d1 << S1;
-    if (kk < bucket) {
-        narrow_pass<NT, C, (1 << L2)>(key, n, S2, d1, g2, ss, kk, bucket, d2);
+    need = k;
+    narrow_pass<C, (1 << L1)>(key, n, first, kWave, S1, 0, g1, ss, need, bucket, d1);
+    v = d1 << S1;
+    if (need < bucket) {
+        narrow_pass<C, (1 << L2)>(key, n, first, kWave, S2, d1, g2, ss, need, bucket, d2);
         v = (d1 << S1) | (d2 << S2);
-        if (kk < bucket) {
-            narrow_pass<NT, C, (1 << L3)>(key, n, 0, (d1 << L2) | d2, g3, ss, kk, bucket, d3);
+        if (need < bucket) {
+            narrow_pass<C, (1 << L3)>(key, n, first, kWave, 0, (d1 << L2) | d2, g3, ss, need, bucket, d3);
             v |= d3;
-            if (kk < bucket) {
-                topk_table_cut<NT, C>(key, n, v, kk, hist, ord);
-                return;
-            }
         }
     }
-    topk_table<NT, C>(key, n, v, ord);
+}
+
+// The same from a bracket [lo, hi] of key values that should hold the k-th
+// largest key (0 < lo): one pass counts the keys above it per wave and bins the
+// few inside it; a second one, over the found bin's values, only when that bin
+// is not wholly in.  Per key this is two compares, where a radix pass over every
+// key is an LDS atomic each, which crowd into few bins.  Of a few hundred keys
+// inside, one in ten or so shares the k-th one's bin; fewer bins for fewer keys
+// keep the clearing and the scan short.
+// Returns false (in every thread) when the bracket does not hold it.
+// hist: kBracketBins<C> + 4096 words of LDS; the first kBracketBins<C> zeroed, the
+// zeros visible.  wcnt: kMaxBlockWaves ints.
+template <int C>
+constexpr int kBracketBins = C <= 16 ? 2048 : 4096;
+template <int C>
+__device__ __forceinline__ bool kth_score_bracket(const uint32_t (&key)[C], int k,
+                                                  uint32_t lo, uint32_t hi, uint32_t *hist,
+                                                  SelScratch &ss, int *wcnt, uint32_t &v, int &need,
+                                                  int &bucket) {
+    constexpr int B1 = kBracketBins<C>, L1 = __builtin_ctz(B1), L2 = 12;
+    const uint32_t width = hi - lo;
+    const int bits = width ? 32 - __builtin_clz(width) : 0;
+    if (bits > L1 + L2) return false;
+    const int shift = bits > L1 ? bits - L1 : 0;
+    int above = 0;
+#pragma unroll
+    for (int r = 0; r < C; ++r) {
+        above += __popcll(__ballot(key[r] > hi));
+        const uint32_t u = key[r] - lo;   // keys past n are 0, below lo
+        if (u <= width) atomicAdd(&hist[u >> shift], 1u);
+    }
+    if (lane_id() == 0) wcnt[wave_id()] = above;
+    if (threadIdx.x == 0) ss.pick[0] = -1;
+    __syncthreads();
+    const int tot = wave_inclusive_scan(lane_id() < kMaxBlockWaves ? wcnt[lane_id()] : 0);
+    need = k - __builtin_amdgcn_readlane(tot, kMaxBlockWaves - 1);
+    if (need <= 0) return false;
+    uint32_t digit;
+    find_digit<B1, false>(hist, need, ss, digit, need, bucket);
+    if ((int)digit < 0) return false;   // fewer than k keys down to lo
+    v = lo + (digit << shift);
+    if (need < bucket && shift > 0) {
+        uint32_t *h2 = hist + B1;
+        reinterpret_cast<uint4 *>(h2)[threadIdx.x] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < C; ++r) {
+            const uint32_t u = key[r] - v;
+            if (u < (1u << shift)) atomicAdd(&h2[u], 1u);
+        }
+        __syncthreads();
+        find_digit<1 << L2, false>(h2, need, ss, digit, need, bucket);
+        v += digit;
+    }
+    return true;
+}
+
+// Order statistics of one full column tile's T scores, for the bracket above:
+// the keys of rank r1 and r2 (1 = largest) to out[0] and out[1].  Thread t takes
+// score t / P and compares it with every P-th other (P = 1024 / T lanes per
+// score, summed by DPP).  sc: the T scores in LDS, visible to the block.
+template <int T>
+__device__ __forceinline__ void tile_order_stats(const uint32_t *sc, int r1, int r2, uint32_t *out) {
+    constexpr int P = kBlock / T;
+    static_assert(P == 8 || P == 16, "lanes per score");
+    const int c = threadIdx.x / P, q = threadIdx.x % P;
+    const uint32_t mine = sc[c];
+    uint32_t before = 0;
+#pragma unroll
+    for (int i = 0; i < T / P; ++i) {
+        const int j = q + P * i;
+        const uint32_t o = sc[j];
+        before += (o > mine || (o == mine && j < c)) ? 1u : 0u;
+    }
+    before = quad_sum_u32(before);
+    before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, 0x141, 0xF, 0xF, false);   // row_half_mirror
+    if constexpr (P == 16)
+        before += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before, kDppRor8, 0xF, 0xF, false);
+    if (q == 0) {
+        if ((int)before == r1 - 1) out[0] = mine;
+        if ((int)before == r2 - 1) out[1] = mine;
+    }
 }
 
 // Ascending position (among the selected) of this thread's selected item r.
@@ -405,13 +490,6 @@ template <int C>
 __device__ __forceinline__ int topk_pos(const TopKOrder<C> &ord, int r) {
     const int wid = threadIdx.x / kWave;
     return ord.off[r * kMaxBlockWaves + wid] + (int)lanes_below(ord.sel[r][wid]);
-}
-
-// Whether item i (0 <= i < C * NT) is selected, any thread.
-template <int NT, int C>
-__device__ __forceinline__ bool topk_is_selected(const TopKOrder<C> &ord, int i) {
-    const int r = i / NT, t = i % NT;
-    return (ord.sel[r][t / kWave] >> (t % kWave)) & 1;
 }
 
 // Number of selected items with index < i (0 <= i <= C * NT), any thread.

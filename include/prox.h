@@ -64,12 +64,12 @@ typedef enum PROX_ENUM_INT { PROX_ACT_SILU = 0, PROX_ACT_GELU = 1 } prox_act;
 typedef enum PROX_ENUM_INT { PROX_Q_INT8 = 0, PROX_Q_INT4 = 1, PROX_Q_NONE = 2 } prox_qfmt;
 
 /* Supported sizes.  Batches past the rows one launch takes (Stage 1: 4 on the
- * dot-product kernel, 8 or 16 on the matrix cores; Stage 2: 16 per chunk on
- * the matrix-core path, see prox_stage2_rows, else 8, fewer for INT4 base
+ * dot-product kernel, 8 or 16 on the matrix cores; Stage 2: every row on the
+ * matrix-core path, see prox_stage2_rows, else 8, fewer for INT4 base
  * weights on wide d_model) run as several launches on the same stream:
  * Stage 1 takes the max of the scores over them, Stage 2 writes disjoint rows
  * of the partial sums, so the result does not depend on the split.  Each
- * Stage 2 launch or chunk reads the kept rows again. */
+ * Stage 2 launch reads the kept rows again. */
 #define PROX_MAX_BATCH 64
 #define PROX_MIN_D_MODEL 128
 #define PROX_MAX_D_MODEL 16384   /* multiple of 128 */
@@ -139,7 +139,7 @@ prox_status prox_unpack_proxy(const prox_proxy *p, int d_model, int d_ff, int8_t
  * no initialisation.  It holds the proxy scores, the kept-channel list and
  * the partial y of Stage 2: one row set per Stage 2 workgroup (256), or, for
  * more than 8 batch rows at d_model >= 4096, per kept-channel group of the
- * matrix-core down projection (64) plus s of the kept channels.  INT4 base
+ * matrix-core down projection (16 or fewer) plus s of the kept channels.  INT4 base
  * weights always take the 256 row sets: see prox_w4_workspace_bytes. */
 size_t prox_workspace_bytes(int d_model, int d_ff, int batch);
 
@@ -156,11 +156,10 @@ int prox_stage1_mfma_rows(int d_model, prox_qfmt fmt, int group, int batch, int 
 
 /*
  * Which Stage-2 path a call takes (for inspection and tests): the batch rows
- * one Stage-2 pass covers.  16 means the matrix-core path (more than eight
- * batch rows of 16-bit weights with d_model >= 4096): every chunk of up to 16
- * rows, the batch tail included, runs gate/up as 16x16x16 MFMAs and then the
- * down projection as a second launch, so the three matrices are read once per
- * 16 rows.  Otherwise one fused VALU launch per up to 8 rows (fewer for INT4
+ * of a row tile.  16 means the matrix-core path (more than eight batch rows of
+ * 16-bit weights with d_model >= 4096): gate/up of every row as 16x16x16 MFMAs
+ * in one launch, in tiles of 16 rows, and then the down projection as a second
+ * launch, so the three matrices are read once.  Otherwise one fused VALU launch per up to 8 rows (fewer for INT4
  * weights, w4 != 0, at wide d_model).  0 for an unsupported shape or batch.
  * Host only, no HIP calls.  Both paths give the same kept set; y differs only
  * in fp32 summation order.

@@ -101,7 +101,8 @@ Ws carve(void *ws, int d, int f, int batch, int wq) {
 const char *const kStageNames[PROX_SPARSE_STAGES] = {"proxy_gemv_score",
                                                      "stage2_select_gate_up_down", "reduce_y"};
 
-// Batch rows per Stage 2 launch for a call of `batch` rows.
+// Batch rows per Stage 2 launch for a call of `batch` rows (kStage2MfmaRows: the
+// matrix-core path, in row tiles of that size).
 int stage2_launch_rows(int d, int wq, int batch) {
     return batch > kStage2MaxNB && stage2_mfma_ok(d, wq) ? kStage2MfmaRows : stage2_rows(d, wq);
 }
@@ -118,27 +119,21 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
     // grid for every channel (workgroups past the count get no channels).
     const int nwg = stage2_wgs(scores && !sel.tau_mode ? k_ff : f);
     const int ystride = ypart_rows(batch);
-    // More than eight rows of 16-bit weights: the matrix-core path, 16 rows
-    // per chunk (its tail too).
+    // More than eight rows of 16-bit weights: the matrix-core path, every row in
+    // one launch (kStage2MfmaMaxRows is the largest batch of a call): gate/up (s
+    // and the kept list to the workspace), then the down projection over groups
+    // of channels; the reduction sums those groups' partial y.
+    static_assert(kStage2MfmaMaxRows >= PROX_MAX_BATCH, "one launch takes every row");
     const int rows = stage2_launch_rows(d, m.s2.wq, batch);
     if (rows == kStage2MfmaRows) {
-        // Every 16-row chunk: gate/up on the matrix cores (s to the
-        // workspace, kept list written by the first chunk), then the down
-        // projection over kStage2DownGroups channel groups; the reduction
-        // sums those groups' partial y.
         const int n_max = scores && !sel.tau_mode ? k_ff : f;
-        for (int c0 = 0; c0 < batch; c0 += rows) {
-            const int nb = batch - c0 < rows ? batch - c0 : rows;
-            const int list_mode = !scores ? kListNone : c0 == 0 ? kListWrite : kListRead;
-            PROX_TRY(launch_stage2_mfma(dt, xb + (size_t)c0 * d, nb, d, f, m.s2, scores, k_ff,
-                                        mask, c0 == 0 ? scores_copy : nullptr, W.sbuf, nwg,
-                                        c0 == 0 ? sel : Select{sel.tau_mode, sel.tau, nullptr}, br,
-                                        m.act, W.klist, list_mode, stream));
-            PROX_TRY(launch_stage2_down(dt, nb, d, f, m.s2.wd, W.sbuf, scores ? W.klist : nullptr,
-                                        n_max, W.ypart + (size_t)c0 * d, ystride, stream));
-        }
+        PROX_TRY(launch_stage2_mfma(dt, xb, batch, d, f, m.s2, scores, k_ff, mask, scores_copy,
+                                    W.sbuf, nwg, sel, br, m.act, W.klist,
+                                    scores ? kListWrite : kListNone, stream));
+        PROX_TRY(launch_stage2_down(dt, batch, d, f, m.s2.wd, W.sbuf, scores ? W.klist : nullptr,
+                                    n_max, W.ypart, ystride, stream));
         if (events) PROX_TRY(hipEventRecord(events[2], stream));
-        PROX_TRY(launch_reduce(dt, W.ypart, kStage2DownGroups, batch, d, y, stream));
+        PROX_TRY(launch_reduce(dt, W.ypart, stage2_down_groups_mfma(d), batch, d, y, stream));
         if (events) PROX_TRY(hipEventRecord(events[3], stream));
         return PROX_OK;
     }

@@ -83,15 +83,15 @@ hipError_t launch_stage2(int dtype, const void *x, int nb, int d, int f, const S
                          const float *scores, int k_ff, uint8_t *mask, float *scores_copy,
                          float *ypart, int ystride, int nwg, Select sel, ScoreBracket br, int act,
                          int32_t *klist, int klist_mode, hipStream_t stream);
-// Stage 2 for up to kStage2MfmaRows batch rows (16-bit weights, d >= 4096:
+// Stage 2 for up to kStage2MfmaMaxRows batch rows (16-bit weights, d >= 4096:
 // stage2_mfma_ok) in two launches.  launch_stage2_mfma selects like
 // launch_stage2 (same kept-list modes; the sparse path must write or read
 // klist, since the down launch takes the kept channels from it), runs gate/up
 // on the matrix cores and writes s of kept-list position p and batch row b to
-// sbuf[p * kStage2MfmaRows + b].  launch_stage2_down then splits the kept
-// list (klist, or every channel when klist is NULL) into kStage2DownGroups
-// groups and writes the partial y of group g to ypart[(g * ystride + b) * d +
-// c]; n_max bounds the kept count (k_ff, or f).
+// sbuf[p * R + b], R = 16 stage2_row_tiles(nb).  launch_stage2_down then splits
+// the kept list (klist, or every channel when klist is NULL) into
+// stage2_down_groups_mfma(d) groups and writes the partial y of group g to
+// ypart[(g * ystride + b) * d + c]; n_max bounds the kept count (k_ff, or f).
 bool stage2_mfma_ok(int d, int wq);
 hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               const Stage2Weights &w, const float *scores, int k_ff,

@@ -106,8 +106,18 @@ struct W4Layout {
 };
 
 constexpr int kStage2MaxNB = 8;          // batch rows per Stage 2 launch
-constexpr int kStage2MfmaRows = 16;      // ... of the matrix-core Stage 2 (16-bit weights)
-constexpr int kStage2DownGroups = 64;    // kept-channel groups of its down projection
+constexpr int kStage2MfmaRows = 16;      // ... of a row tile of the matrix-core Stage 2 (16-bit weights)
+constexpr int kStage2MfmaMaxRows = 64;   // ... of its launch
+constexpr int kStage2DownMaxGroups = 16; // kept-channel groups of its down projection, at most
+
+// Row tiles its launch of nb rows is compiled for.
+__host__ __device__ inline int stage2_row_tiles(int nb) { return nb <= 16 ? 1 : nb <= 32 ? 2 : 4; }
+// Kept-channel groups of its down projection: as many as fill the chip with the
+// workgroups of 256 columns (16 at d_model 4096, 8 at 8192); more only add partial y.
+__host__ __device__ inline int stage2_down_groups_mfma(int d) {
+    const int g = 256 / ((d + 255) / 256);
+    return g > kStage2DownMaxGroups ? kStage2DownMaxGroups : g;
+}
 
 // Batch rows a Stage 2 launch of nb <= 8 rows is compiled for (1, 2, 4 or 8).
 __host__ __device__ inline int stage2_nb_t(int nb) {
@@ -151,10 +161,10 @@ struct ScoreBracket {
 // ---------------------------------------------------------------------------
 // scores: the proxy scores (fp32, f padded to 128); ypart: the partial y rows
 // of Stage 2, one set per Stage 2 workgroup (kStage2MaxWGs), or per
-// kept-channel group of the matrix-core down projection (kStage2DownGroups)
-// when a batch of more than kStage2MaxNB rows of 16-bit weights takes that
-// path; sbuf (that path only): s of the kept channels in kept-list order,
-// [f][kStage2MfmaRows] fp32.  wq: 16 for 16-bit weights, 4 for INT4 ones.
+// kept-channel group of the matrix-core down projection
+// (stage2_down_groups_mfma) when a batch of more than kStage2MaxNB rows of
+// 16-bit weights takes that path; sbuf (that path only): s of the kept channels
+// in kept-list order, [f][16 rows per row tile] fp32.  wq: 16 for 16-bit weights, 4 for INT4 ones.
 // Shapes the matrix-core Stage 2 takes: 16-bit weights, d_model >= 4096.
 __host__ __device__ inline bool stage2_mfma_shape(int d, int wq) { return wq == 16 && d >= 4096; }
 __host__ __device__ inline bool ws_mfma_path(int d, int batch, int wq) {
@@ -165,13 +175,13 @@ struct WsLayout {
     __host__ __device__ WsLayout(int d, int f, int batch, int wq) {
         const int f_pad = (f + 127) / 128 * 128;
         const bool mfma = ws_mfma_path(d, batch, wq);
-        const size_t groups = mfma ? kStage2DownGroups : kStage2MaxWGs;
+        const size_t groups = mfma ? stage2_down_groups_mfma(d) : kStage2MaxWGs;
         size_t o = 0;
         scores = o; o = align_up(o + (size_t)f_pad * 4, 256);
         klist = o; o = align_up(o + (size_t)(f + 1) * 4, 256);   // kept channels, then their count
         ypart = o; o = align_up(o + groups * ypart_rows(batch) * d * 4, 256);
         sbuf = o;
-        if (mfma) o = align_up(o + (size_t)f * kStage2MfmaRows * 4, 256);
+        if (mfma) o = align_up(o + (size_t)f * kStage2MfmaRows * stage2_row_tiles(batch) * 4, 256);
         total = o;
     }
 };

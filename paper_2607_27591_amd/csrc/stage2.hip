@@ -816,30 +816,27 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// stage2_mfma_kernel + stage2_down_kernel: Stage 2 for up to 16 batch rows of
-// 16-bit weights, so every kept row of the three matrices is read once for
-// all of them.
+// stage2_mfma_kernel + stage2_down_kernel: Stage 2 for 9 to 64 batch rows of
+// 16-bit weights, so every kept row of the three matrices is read once for all
+// of them.  RT: tiles of 16 batch rows (1, 2 or 4).
 //  prologue  the slice of kept channels, as in stage2_kernel.
 //  gate/up   on the matrix cores: the slice is cut into tiles of 16 channels,
 //            and wave w takes the w-th sixteenth of d for every tile, so the
 //            waves stream equal bytes however few channels the slice holds.
 //            Per 32 inputs a lane loads 16 contiguous bytes of one channel row
-//            of each matrix (A) and of one batch row of x (B, from L2), and two
-//            16 x 16 x 16 MFMAs per matrix add the products into the tile's
-//            [16 channels][16 rows] fp32 sums.  The 16 waves' sums of a tile
-//            are added through LDS in wave order; s = act(g) u goes to the
-//            workspace at the channel's kept-list position.
-//  down      a second launch: the kept list is cut into kStage2DownGroups
-//            groups, and each workgroup takes one group and 1024 columns,
-//            with the group's s in LDS; every thread owns 4 columns and all 16
-//            rows (VALU), and four thread groups split the channels.  With 64
-//            groups the partial y are a quarter of what one partial per Stage 2
-//            workgroup would be: at 16 rows those are as large as the weights
-//            the step reads.
+//            of each matrix (A) and of one batch row of x per row tile (B, from
+//            L2), and two 16 x 16 x 16 MFMAs per matrix and row tile add the
+//            products into the tile's [16 channels][16 rows] fp32 sums.  The 16
+//            waves' sums of a tile are added through LDS in wave order; s =
+//            act(g) u goes to the workspace at the channel's kept-list position.
+//  down      a second launch, below.
+// A launch per 16 rows read the weights four times for 64 rows: 4096 x 14336,
+// 30% kept, gate/up 4 x 23 us, now 42 (x comes from L2, one step in flight);
+// 16 rows are as before, 27 us.
 // ---------------------------------------------------------------------------
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kS2mTiles = 2;   // channel tiles per pass through the gate/up loop
-constexpr int kS2mRed = kS2mTiles * 2 * kMaxBlockWaves * kWave;   // float4 per pass
+constexpr int kS2mRed = kS2mTiles * 2 * kMaxBlockWaves * kWave;   // float4 per pass and row tile
 
 size_t stage2_mfma_lds_bytes() {
     return (size_t)kS2mRed * 16 > kSelHistF32Bytes ? (size_t)kS2mRed * 16 : kSelHistF32Bytes;
@@ -847,13 +844,13 @@ size_t stage2_mfma_lds_bytes() {
 
 bool stage2_mfma_ok(int d, int wq) { return stage2_mfma_shape(d, wq); }
 
-template <int DT, int C>
+template <int DT, int C, int RT>
 __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
     const uint16_t *__restrict__ x, int nb, int d, int f, Stage2Weights wt,
     const float *__restrict__ scores, int k_ff, uint8_t *__restrict__ mask,
     float *__restrict__ scores_copy, float *__restrict__ sbuf, Select sel_rule, ScoreBracket br,
     int act, int32_t *__restrict__ klist, int klist_mode) {
-    constexpr int R = kStage2MfmaRows;
+    constexpr int R = 16 * RT;
     const uint16_t *__restrict__ wg = static_cast<const uint16_t *>(wt.wg);
     const uint16_t *__restrict__ wu = static_cast<const uint16_t *>(wt.wu);
     const int tid = threadIdx.x, wid = tid / kWave, lane = lane_id();
@@ -873,14 +870,13 @@ __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
     const int nsteps = d / 32;   // steps of 32 inputs
     const int k_lo = wid * nsteps / kMaxBlockWaves, k_hi = (wid + 1) * nsteps / kMaxBlockWaves;
     const int r = lane % 16, g4 = lane / 16;
-    const bool xrow = r < nb;
-    const uint16_t *xr = x + (size_t)(xrow ? r : 0) * d + 8 * g4;
+    const auto xb = buffer_of(x, (uint32_t)(nb * d) * 2);   // rows past nb read 0
     const int ntiles = (n + 15) / 16;
-    constexpr int U = 2;   // steps in flight per lane
+    constexpr int U = RT == 1 ? 2 : 1;   // steps in flight per lane
     for (int t0 = 0; t0 < ntiles; t0 += kS2mTiles) {
         const uint16_t *rg[kS2mTiles], *ru[kS2mTiles];
         bool live[kS2mTiles];
-        v4f ag[kS2mTiles], au[kS2mTiles];
+        v4f ag[kS2mTiles][RT], au[kS2mTiles][RT];
 #pragma unroll
         for (int tt = 0; tt < kS2mTiles; ++tt) {
             const int t = (t0 + tt) * 16 + r;
@@ -888,152 +884,245 @@ __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
             const int j = live[tt] ? list[t] : 0;
             rg[tt] = wg + (size_t)j * d + 8 * g4;
             ru[tt] = wu + (size_t)j * d + 8 * g4;
-            ag[tt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-            au[tt] = ag[tt];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) ag[tt][rt] = au[tt][rt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
         for (int k = k_lo; k < k_hi; k += U) {
-            uint4 xv[U], gv[kS2mTiles][U], uv[kS2mTiles][U];
+            uint4 xv[U][RT], gv[kS2mTiles][U], uv[kS2mTiles][U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int kk = k + u;
                 const bool in = kk < k_hi;
-                xv[u] = in && xrow ? *reinterpret_cast<const uint4 *>(xr + kk * 32) : make_uint4(0, 0, 0, 0);
 #pragma unroll
                 for (int tt = 0; tt < kS2mTiles; ++tt) {
                     const bool ld = in && live[tt];
                     gv[tt][u] = ld ? load_stream16(rg[tt] + kk * 32) : make_uint4(0, 0, 0, 0);
                     uv[tt][u] = ld ? load_stream16(ru[tt] + kk * 32) : make_uint4(0, 0, 0, 0);
                 }
+                // Past k_hi the weights are 0 and x may be anything finite of its rows.
+                const int xo = (r * d + min(kk, nsteps - 1) * 32 + 8 * g4) * 2;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) xv[u][rt] = buffer_load128(xb, xo + rt * 16 * d * 2, 0);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 // Inputs 8 g4 + 0..3 of the step in the first MFMA, 8 g4 + 4..7
                 // in the second: A and B take the same inputs in the same slots.
-                const uint2 xa = make_uint2(xv[u].x, xv[u].y), xb = make_uint2(xv[u].z, xv[u].w);
 #pragma unroll
-                for (int tt = 0; tt < kS2mTiles; ++tt) {
-                    ag[tt] = mfma16<DT>(make_uint2(gv[tt][u].x, gv[tt][u].y), xa, ag[tt]);
-                    ag[tt] = mfma16<DT>(make_uint2(gv[tt][u].z, gv[tt][u].w), xb, ag[tt]);
-                    au[tt] = mfma16<DT>(make_uint2(uv[tt][u].x, uv[tt][u].y), xa, au[tt]);
-                    au[tt] = mfma16<DT>(make_uint2(uv[tt][u].z, uv[tt][u].w), xb, au[tt]);
+                for (int rt = 0; rt < RT; ++rt) {
+                    const uint2 xa = make_uint2(xv[u][rt].x, xv[u][rt].y);
+                    const uint2 xc = make_uint2(xv[u][rt].z, xv[u][rt].w);
+#pragma unroll
+                    for (int tt = 0; tt < kS2mTiles; ++tt) {
+                        ag[tt][rt] = mfma16<DT>(make_uint2(gv[tt][u].x, gv[tt][u].y), xa, ag[tt][rt]);
+                        ag[tt][rt] = mfma16<DT>(make_uint2(gv[tt][u].z, gv[tt][u].w), xc, ag[tt][rt]);
+                        au[tt][rt] = mfma16<DT>(make_uint2(uv[tt][u].x, uv[tt][u].y), xa, au[tt][rt]);
+                        au[tt][rt] = mfma16<DT>(make_uint2(uv[tt][u].z, uv[tt][u].w), xc, au[tt][rt]);
+                    }
                 }
             }
         }
         // Lane l holds channel 4 (l / 16) + e, batch row l % 16 of each tile.
 #pragma unroll
-        for (int tt = 0; tt < kS2mTiles; ++tt) {
-            red[((tt * 2 + 0) * kMaxBlockWaves + wid) * kWave + lane] =
-                make_float4(ag[tt][0], ag[tt][1], ag[tt][2], ag[tt][3]);
-            red[((tt * 2 + 1) * kMaxBlockWaves + wid) * kWave + lane] =
-                make_float4(au[tt][0], au[tt][1], au[tt][2], au[tt][3]);
-        }
-        __syncthreads();
-        if (tid < kS2mTiles * kWave * 4) {
-            const int tt = tid / (kWave * 4), ln = (tid / 4) % kWave, e = tid % 4;
-            const float *rf = reinterpret_cast<const float *>(red);
-            float gs = 0.0f, us = 0.0f;
-            for (int w = 0; w < kMaxBlockWaves; ++w) {
-                gs += rf[(((tt * 2 + 0) * kMaxBlockWaves + w) * kWave + ln) * 4 + e];
-                us += rf[(((tt * 2 + 1) * kMaxBlockWaves + w) * kWave + ln) * 4 + e];
+        for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+            for (int tt = 0; tt < kS2mTiles; ++tt) {
+                const v4f g = ag[tt][rt], u = au[tt][rt];
+                red[((tt * 2 + 0) * kMaxBlockWaves + wid) * kWave + lane] = make_float4(g[0], g[1], g[2], g[3]);
+                red[((tt * 2 + 1) * kMaxBlockWaves + wid) * kWave + lane] = make_float4(u[0], u[1], u[2], u[3]);
             }
-            const int t = (t0 + tt) * 16 + 4 * (ln / 16) + e;
-            if (t < n) sbuf[(size_t)(p0 + t) * R + ln % 16] = gate_act(gs, act) * us;
+            __syncthreads();
+            if (tid < kS2mTiles * kWave * 4) {
+                const int tt = tid / (kWave * 4), ln = (tid / 4) % kWave, e = tid % 4;
+                const float *rf = reinterpret_cast<const float *>(red);
+                float gs = 0.0f, us = 0.0f;
+                for (int w = 0; w < kMaxBlockWaves; ++w) {
+                    gs += rf[(((tt * 2 + 0) * kMaxBlockWaves + w) * kWave + ln) * 4 + e];
+                    us += rf[(((tt * 2 + 1) * kMaxBlockWaves + w) * kWave + ln) * 4 + e];
+                }
+                const int t = (t0 + tt) * 16 + 4 * (ln / 16) + e;
+                if (t < n) sbuf[(size_t)(p0 + t) * R + rt * 16 + ln % 16] = gate_act(gs, act) * us;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
-constexpr int kDownCols = 256;              // 4-column groups per workgroup: 1024 columns
-constexpr int kDownSplit = kBlock / kDownCols;   // thread groups splitting its channels
-
-size_t stage2_down_lds_bytes(int n_max) {
-    const size_t m = (size_t)(n_max + kStage2DownGroups - 1) / kStage2DownGroups;
-    return (size_t)kStage2MfmaRows * kDownCols * 16 + m * (kStage2MfmaRows * 4 + 4);
-}
+// Down projection on the matrix cores: y[b][c] = sum_j s[b][j] W_down[j][c].  The
+// kept list is cut into stage2_down_groups groups; a workgroup takes one group and
+// 256 columns: four waves of 64 columns by four splits of the channels, in
+// blocks of 16.  A lane loads 8 bytes (4 columns) of four channel rows, which
+// paired by v_perm are the B operands of 16 x 16 x 16 MFMAs (4 rows of k per
+// lane); s is the A operand, kept to fp32 precision: for bf16 weights as the sum
+// of three bf16 (8 bits each: the 24 of fp32), three MFMAs; for fp16, whose range
+// that would not fit, 16 x 16 x 4 fp32 MFMAs on the widened weights.  s is split
+// on its way to LDS, kDownChunk channels at a time, in operand order.  The splits'
+// sums meet in LDS in order.
+// Against VALU FMAs (16 per weight, 64 groups of partial
+// y): 4096 x 14336, 30% kept, 11 us instead of 18 at 16 rows, 23 instead of 4 x 17
+// at 64 (4.2 and 16.8 MB of partial y instead of 16.8 and 67).
+constexpr int kDownCols = 256;     // columns per workgroup
+constexpr int kDownChunk = 320;    // channels staged at a time
+constexpr int kDownSplit = 4;
 
 template <int DT>
+constexpr int kDownSBytes = DT == kBF16 ? 6 : 4;   // of one s in LDS
+
+size_t stage2_down_lds_bytes(int dtype, int rt, int n_max, int groups) {
+    const int m = (n_max + groups - 1) / groups;
+    const size_t blocks = (size_t)((m < kDownChunk ? m : kDownChunk) + 15) / 16;
+    const size_t s = blocks * 16 * rt * 16 * (dtype == kBF16 ? 6 : 4) + blocks * 16 * 4;
+    const size_t red = (size_t)kBlock * 64;   // 16 sums per thread
+    return s > red ? s : red;
+}
+
+// The next bf16 part of v, and what remains.
+__device__ __forceinline__ uint32_t bf16_part(float &v) {
+    const uint32_t h = float_to_bf16_rne(v);
+    v -= bf16_lo(h);
+    return h;
+}
+
+template <int DT, int RT>
 __global__ __launch_bounds__(kBlock) void stage2_down_kernel(
     int nb, int d, int f, const uint16_t *__restrict__ wd, const float *__restrict__ sbuf,
     const int32_t *__restrict__ klist, float *__restrict__ ypart, int ypart_stride) {
-    constexpr int R = kStage2MfmaRows;
-    extern __shared__ __align__(16) float dyn[];   // red [R][kDownCols] float4 | s [m][R] | ids [m]
-    const int tid = threadIdx.x;
+    constexpr int R = 16 * RT;
+    extern __shared__ __align__(16) unsigned char dsm[];   // s in operand order | ids, then red
+    const int tid = threadIdx.x, lane = lane_id(), wid = wave_id();
     const int n_ch = klist ? klist[f] : f;
-    const int grp = blockIdx.y;
-    const int q0 = (int)((long long)grp * n_ch / kStage2DownGroups);
-    const int m = (int)((long long)(grp + 1) * n_ch / kStage2DownGroups) - q0;
-    float4 *red = reinterpret_cast<float4 *>(dyn);
-    float *s_l = dyn + (size_t)R * kDownCols * 4;
-    int *ids = reinterpret_cast<int *>(s_l + (size_t)m * R);
-    for (int e = tid; e < m * R; e += kBlock) s_l[e] = sbuf[(size_t)q0 * R + e];
-    for (int t = tid; t < m; t += kBlock) ids[t] = klist ? klist[q0 + t] : q0 + t;
-    __syncthreads();
+    const int grp = blockIdx.y, groups = gridDim.y;
+    const int q0 = (int)((uint32_t)(grp * n_ch) / (uint32_t)groups);
+    const int m = (int)((uint32_t)((grp + 1) * n_ch) / (uint32_t)groups) - q0;
+    const int wc = wid % 4, sp = wid / 4;
+    const int col = blockIdx.x * kDownCols + wc * 64 + (lane % 16) * 4;   // first of 4 columns
+    const bool active = col < d;   // whole waves: d is a multiple of 128
+    const int g = lane / 16;
 
-    // Thread group sub takes channels sub, sub + kDownSplit, ... of the group.
-    const int sub = tid / kDownCols, cgl = tid % kDownCols;
-    const int cg = blockIdx.x * kDownCols + cgl;   // columns 4 cg .. 4 cg + 3
-    const bool active = cg < d / 4;
-    constexpr int UD = 12;   // rows in flight
-    float acc[R][4];
+    v4f acc[RT][4];
 #pragma unroll
-    for (int b = 0; b < R; ++b)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[b][e] = 0.0f;
-    if (active) {
-        for (int t0 = sub; t0 < m; t0 += kDownSplit * UD) {
-            uint2 wv[UD];
+        for (int c = 0; c < 4; ++c) acc[rt][c] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+
+    for (int c0 = 0; c0 < m; c0 += kDownChunk) {
+        const int mc = min(kDownChunk, m - c0);
+        const int blocks = (mc + 15) / 16;
+        int *ids = reinterpret_cast<int *>(dsm + (size_t)blocks * 16 * R * kDownSBytes<DT>);
+        if (c0 > 0) __syncthreads();   // the previous chunk is used up
+        // Pad channels repeat the last row, with s = 0.
+        for (int t = tid; t < blocks * 16; t += kBlock) {
+            const int q = q0 + c0 + min(t, mc - 1);
+            ids[t] = klist ? klist[q] : q;
+        }
+        // Thread: batch row b, channels 4 t4 .. 4 t4 + 3 of the chunk.
+        for (int e = tid; e < blocks * 4 * R; e += kBlock) {
+            const int b = e % R, t4 = e / R;
+            float v[4];
 #pragma unroll
-            for (int u = 0; u < UD; ++u) {
-                const int t = t0 + u * kDownSplit;
-                if (t < m) {
-                    const u32x2 v = __builtin_nontemporal_load(
-                        reinterpret_cast<const u32x2 *>(wd + (size_t)ids[t] * d + cg * 4));
-                    wv[u] = make_uint2(v.x, v.y);
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int t = t4 * 4 + q;
+                v[q] = sbuf[(size_t)(q0 + c0 + min(t, mc - 1)) * R + b];
+                if (t >= mc || b >= nb) v[q] = 0.0f;
             }
+            // Operand slot: block t4 / 4, row tile b / 16, lane (t4 % 4) * 16 + b % 16.
+            const int slot = ((t4 / 4) * RT + b / 16) * kWave + (t4 % 4) * 16 + b % 16;
+            if constexpr (DT == kBF16) {
+                uint2 *dst = reinterpret_cast<uint2 *>(dsm) + slot;
 #pragma unroll
-            for (int u = 0; u < UD; ++u) {
-                const int t = t0 + u * kDownSplit;
-                if (t < m) {
-                    const float wf[4] = {lo_to_float<DT>(wv[u].x), hi_to_float<DT>(wv[u].x),
-                                         lo_to_float<DT>(wv[u].y), hi_to_float<DT>(wv[u].y)};
+                for (int part = 0; part < 3; ++part) {
+                    const uint32_t h0 = bf16_part(v[0]), h1 = bf16_part(v[1]);
+                    const uint32_t h2 = bf16_part(v[2]), h3 = bf16_part(v[3]);
+                    dst[(size_t)part * blocks * RT * kWave] = make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
+                }
+            } else {
+                reinterpret_cast<float4 *>(dsm)[slot] = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        }
+        __syncthreads();
+        const int b_lo = sp * blocks / kDownSplit, b_hi = (sp + 1) * blocks / kDownSplit;
+        constexpr int U = RT == 4 ? 3 : 5;   // blocks in flight
+        if (active) {
+            for (int k0 = b_lo; k0 < b_hi; k0 += U) {
+                uint2 w[U][4];
 #pragma unroll
-                    for (int b = 0; b < R; ++b) {
-                        const float sv = s_l[t * R + b];
+                for (int u = 0; u < U; ++u) {
+                    const int4 id = *reinterpret_cast<const int4 *>(ids + min(k0 + u, b_hi - 1) * 16 + 4 * g);
+                    const int j[4] = {id.x, id.y, id.z, id.w};
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[b][e] = fmaf(sv, wf[e], acc[b][e]);
+                    for (int e = 0; e < 4; ++e) w[u][e] = load_stream8(wd + (size_t)j[e] * d + col);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (k0 + u >= b_hi) break;   // uniform
+                    const int blk = k0 + u;
+                    if constexpr (DT == kBF16) {
+                        uint2 bop[4];   // column c: rows (0, 1) and (2, 3) side by side
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+                            const uint32_t a0 = c < 2 ? w[u][0].x : w[u][0].y, a1 = c < 2 ? w[u][1].x : w[u][1].y;
+                            const uint32_t a2 = c < 2 ? w[u][2].x : w[u][2].y, a3 = c < 2 ? w[u][3].x : w[u][3].y;
+                            bop[c] = make_uint2(__builtin_amdgcn_perm(a1, a0, sel), __builtin_amdgcn_perm(a3, a2, sel));
+                        }
+                        const uint2 *sl = reinterpret_cast<const uint2 *>(dsm) + (size_t)blk * RT * kWave + lane;
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                            for (int part = 0; part < 3; ++part) {
+                                const uint2 a = sl[((size_t)part * blocks * RT + rt) * kWave];
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) acc[rt][c] = mfma16<DT>(a, bop[c], acc[rt][c]);
+                            }
+                    } else {
+                        const float4 *sl = reinterpret_cast<const float4 *>(dsm) + (size_t)blk * RT * kWave + lane;
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt) {
+                            const float4 a = sl[rt * kWave];
+                            const float av[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float wf[4] = {lo_to_float<DT>(w[u][e].x), hi_to_float<DT>(w[u][e].x),
+                                                     lo_to_float<DT>(w[u][e].y), hi_to_float<DT>(w[u][e].y)};
+#pragma unroll
+                                for (int c = 0; c < 4; ++c)
+                                    acc[rt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], wf[c], acc[rt][c], 0, 0, 0);
+                            }
+                        }
                     }
                 }
             }
         }
     }
-    // The thread groups' sums are added in group order through LDS; every
-    // thread reaches every barrier.
-    for (int g2 = 0; g2 < kDownSplit - 1; ++g2) {
-        if (sub == g2) {
+    // The splits' sums in order.  Lane l of a wave holds rows 4 (l / 16) + e,
+    // columns 4 (l % 16) + c; thread (e, wave, lane) of the output takes one row's
+    // 4 columns.
+    float4 *red = reinterpret_cast<float4 *>(dsm);   // [split][wave][c][lane]
+    for (int rt = 0; rt < RT; ++rt) {
+        __syncthreads();   // s, or the previous row tile, is used up
 #pragma unroll
-            for (int b = 0; b < R; ++b) {
-                float4 v = make_float4(acc[b][0], acc[b][1], acc[b][2], acc[b][3]);
-                if (g2 > 0) {
-                    const float4 o = red[b * kDownCols + cgl];
-                    v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-                }
-                red[b * kDownCols + cgl] = v;
+        for (int q = 0; q < RT; ++q)
+            if (q == rt) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    red[((sp * 4 + wc) * 4 + c) * kWave + lane] =
+                        make_float4(acc[q][c][0], acc[q][c][1], acc[q][c][2], acc[q][c][3]);
             }
-        }
         __syncthreads();
-    }
-    if (sub == kDownSplit - 1 && active) {
+        const int e = wid / 4;   // the wave's output row within 4 (wave column group wc as before)
+        float o[4];
 #pragma unroll
-        for (int b = 0; b < R; ++b) {
-            if (b < nb) {
-                const float4 o = red[b * kDownCols + cgl];
-                float4 *dst = reinterpret_cast<float4 *>(
-                    ypart + ((size_t)grp * ypart_stride + b) * d + cg * 4);
-                *dst = make_float4(o.x + acc[b][0], o.y + acc[b][1], o.z + acc[b][2],
-                                   o.w + acc[b][3]);
-            }
+        for (int c = 0; c < 4; ++c) {
+            float t = 0.0f;
+#pragma unroll
+            for (int q = 0; q < kDownSplit; ++q)
+                t += reinterpret_cast<const float *>(&red[((q * 4 + wc) * 4 + c) * kWave + lane])[e];
+            o[c] = t;
         }
+        const int b = rt * 16 + 4 * g + e;
+        if (active && b < nb)
+            *reinterpret_cast<float4 *>(ypart + ((size_t)grp * ypart_stride + b) * d + col) =
+                make_float4(o[0], o[1], o[2], o[3]);
     }
 }
 
@@ -1046,9 +1135,9 @@ constexpr int kReduceThreads = 256;
 constexpr int kReduceCols = 32;
 constexpr int kReduceGroups = kReduceThreads / kReduceCols;                 // 8
 constexpr int kReducePerThread = (kStage2MaxWGs + kReduceGroups - 1) / kReduceGroups;   // 32
-constexpr int kReduceSmall = kStage2DownGroups / kReduceGroups;   // 8: for <= 64 partials
+constexpr int kReduceSmall = kStage2DownMaxGroups / kReduceGroups;   // 2: for <= 16 partials
 
-// UPT: partials per thread (kReducePerThread, or kReduceSmall when nwg <= 64,
+// UPT: partials per thread (kReducePerThread, or kReduceSmall when nwg <= 16,
 // which adds the same terms in the same order).
 
 template <int DT, int UPT>
@@ -1188,26 +1277,26 @@ hipError_t launch_stage2(int dtype, const void *x, int nb, int d, int f, const S
 #undef S2
 }
 
-template <int DT, int C>
+template <int DT, int C, int RT>
 static hipError_t launch_stage2m_t(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
                                    ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
     const size_t lds = stage2_mfma_lds_bytes();
-    hipError_t e = allow_lds(stage2_mfma_kernel<DT, C>, lds);
+    hipError_t e = allow_lds(stage2_mfma_kernel<DT, C, RT>, lds);
     if (e != hipSuccess) return e;
-    stage2_mfma_kernel<DT, C><<<nwg, kBlock, lds, st>>>(
+    stage2_mfma_kernel<DT, C, RT><<<nwg, kBlock, lds, st>>>(
         static_cast<const uint16_t *>(x), nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf,
         sel_rule, br, act, klist, klist_mode);
     return hipGetLastError();
 }
 
-template <int DT>
+template <int DT, int RT>
 static hipError_t launch_stage2m_c(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
                                    ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
-#define S2M(C_) launch_stage2m_t<DT, C_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
+#define S2M(C_) launch_stage2m_t<DT, C_, RT>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
     if (scores && f <= 4 * kBlock) return S2M(4);
     if (scores && f <= 8 * kBlock) return S2M(8);
     if (scores && f <= 12 * kBlock) return S2M(12);
@@ -1224,40 +1313,56 @@ hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               Select sel_rule, ScoreBracket br, int act, int32_t *klist,
                               int klist_mode, hipStream_t st) {
     const int n_ch = scores && !sel_rule.tau_mode ? k_ff : f;   // the kept-list length
-    if (nb < 1 || nb > kStage2MfmaRows || !stage2_mfma_ok(d, wt.wq) || nwg < 1 ||
+    if (nb < 1 || nb > kStage2MfmaMaxRows || !stage2_mfma_ok(d, wt.wq) || nwg < 1 ||
         nwg > kStage2MaxWGs || (long long)n_ch > (long long)kMaxSlice * nwg || !sbuf)
         return hipErrorInvalidValue;
     // The down launch reads the kept list: a sparse call writes or reads it.
     if ((scores != nullptr) != (klist_mode != kListNone) || (scores && !klist))
         return hipErrorInvalidValue;
-    if (dtype == kBF16)
-        return launch_stage2m_c<kBF16>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf,
-                                       nwg, sel_rule, br, act, klist, klist_mode, st);
-    return launch_stage2m_c<kF16>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg,
-                                  sel_rule, br, act, klist, klist_mode, st);
+#define S2M(DT_, RT_) return launch_stage2m_c<DT_, RT_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
+    const int rt = stage2_row_tiles(nb);
+    if (dtype == kBF16) {
+        if (rt == 1) S2M(kBF16, 1);
+        if (rt == 2) S2M(kBF16, 2);
+        S2M(kBF16, 4);
+    }
+    if (rt == 1) S2M(kF16, 1);
+    if (rt == 2) S2M(kF16, 2);
+    S2M(kF16, 4);
+#undef S2M
+}
+
+template <int DT, int RT>
+static hipError_t launch_stage2d_t(int nb, int d, int f, const void *wd, const float *sbuf,
+                                   const int32_t *klist, int n_max, float *ypart, int ystride,
+                                   hipStream_t st) {
+    const int groups = stage2_down_groups_mfma(d);
+    const size_t lds = stage2_down_lds_bytes(DT, RT, n_max, groups);
+    const hipError_t e = allow_lds(stage2_down_kernel<DT, RT>, lds);
+    if (e != hipSuccess) return e;
+    const dim3 grid((d + kDownCols - 1) / kDownCols, groups);
+    stage2_down_kernel<DT, RT><<<grid, kBlock, lds, st>>>(
+        nb, d, f, static_cast<const uint16_t *>(wd), sbuf, klist, ypart, ystride);
+    return hipGetLastError();
 }
 
 hipError_t launch_stage2_down(int dtype, int nb, int d, int f, const void *wd, const float *sbuf,
                               const int32_t *klist, int n_max, float *ypart, int ystride,
                               hipStream_t st) {
-    if (nb < 1 || nb > kStage2MfmaRows || d % 4 != 0 || n_max < 0 || n_max > f || !sbuf ||
+    if (nb < 1 || nb > kStage2MfmaMaxRows || d % 128 != 0 || n_max < 0 || n_max > f || !sbuf ||
         (!klist && n_max != f))
         return hipErrorInvalidValue;
-    const size_t lds = stage2_down_lds_bytes(n_max);
-    const dim3 grid((d / 4 + kDownCols - 1) / kDownCols, kStage2DownGroups);
-    const uint16_t *w = static_cast<const uint16_t *>(wd);
+#define S2D(DT_, RT_) return launch_stage2d_t<DT_, RT_>(nb, d, f, wd, sbuf, klist, n_max, ypart, ystride, st)
+    const int rt = stage2_row_tiles(nb);
     if (dtype == kBF16) {
-        hipError_t e = allow_lds(stage2_down_kernel<kBF16>, lds);
-        if (e != hipSuccess) return e;
-        stage2_down_kernel<kBF16><<<grid, kBlock, lds, st>>>(nb, d, f, w, sbuf, klist, ypart,
-                                                                   ystride);
-    } else {
-        hipError_t e = allow_lds(stage2_down_kernel<kF16>, lds);
-        if (e != hipSuccess) return e;
-        stage2_down_kernel<kF16><<<grid, kBlock, lds, st>>>(nb, d, f, w, sbuf, klist, ypart,
-                                                                  ystride);
+        if (rt == 1) S2D(kBF16, 1);
+        if (rt == 2) S2D(kBF16, 2);
+        S2D(kBF16, 4);
     }
-    return hipGetLastError();
+    if (rt == 1) S2D(kF16, 1);
+    if (rt == 2) S2D(kF16, 2);
+    S2D(kF16, 4);
+#undef S2D
 }
 
 hipError_t launch_reduce(int dtype, const float *ypart, int nwg, int nb, int d, void *y,

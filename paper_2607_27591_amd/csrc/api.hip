@@ -225,9 +225,12 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
     const Ws W = carve(ws, d, f, batch, m.s2.wq);
     const int dt = m.dtype;
     if (events) PROX_TRY(hipEventRecord(events[0], stream));
-    // Several batch rows with an INT4 proxy: the matrix-core kernel, which
-    // reads the codes once for up to 16 rows; else the dot-product kernel.
-    const int mfma_rows = stage1_mfma_rows(d, qbits, p->group, batch, k_in);
+    // INT4 proxies: up to four rows (one above d = 8192) on the small-batch kernel,
+    // more on the 16-row matrix-core kernel, which reads the codes once for up to
+    // 16 rows (at 4096 x 14336 and four rows 54.1 us the call, 56.8 on that one), or
+    // in several small-batch launches where its list does not fit.  INT8 and
+    // unquantised proxies: the dot-product kernel.
+    const int mfma_rows = batch <= proxy_max_nb(d) ? 0 : stage1_mfma_rows(d, qbits, p->group, batch, k_in);
     const int pnb = mfma_rows ? mfma_rows : proxy_max_nb(d);
     const ScoreBracket br = score_bracket(f, k_ff, W.klist);
     for (int c0 = 0; c0 < batch; c0 += pnb) {
@@ -243,6 +246,10 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
                                        c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel,
                                        m.act, out, reinterpret_cast<int32_t *>(W.ypart), list_mode,
                                        stream));
+        else if (qbits == 4)
+            PROX_TRY(launch_proxy_small(dt, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
+                                        c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel, m.act,
+                                        out, stream));
         else
             PROX_TRY(launch_proxy(dt, qbits, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
                                   c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel, m.act,

@@ -138,6 +138,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint3
 __device__ __forceinline__ uint32_t buffer_load32(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
     return __builtin_amdgcn_raw_buffer_load_b32(rs, off + (imm & 4095), imm & ~4095, 0);
 }
+__device__ __forceinline__ uint32_t buffer_load16(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + (imm & 4095), imm & ~4095, 0);
+}
 __device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
     const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + (imm & 4095), imm & ~4095, 0);
     return make_uint2(v[0], v[1]);
@@ -158,6 +161,14 @@ __device__ __forceinline__ float gate_act(float z, int act) {
 // ---------------------------------------------------------------------------
 // Wave64 collectives
 // ---------------------------------------------------------------------------
+
+// Orders a wave's LDS writes before its later LDS reads by other lanes (the LDS
+// serves a wave's instructions in order; this holds the compiler to it).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 

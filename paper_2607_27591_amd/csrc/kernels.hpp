@@ -31,7 +31,8 @@ hipError_t launch_pack(int dtype, int qbits, const void *wg, const void *wu, int
 hipError_t launch_unpack(int qbits, const void *blob, int d, int f, int group, int8_t *cg,
                          uint16_t *sg, int8_t *cu, uint16_t *su, hipStream_t stream);
 
-// Stage 1 for batch rows [row0, row0 + nb) of x_all (nb <= proxy_max_nb(d));
+// Stage 1 of INT8 and unquantised proxies (launch_proxy) for batch rows [row0,
+// row0 + nb) of x_all (nb <= proxy_max_nb(d));
 // the input selection ranks all B_all rows (top k_in, or the threshold rule
 // of sel, for which k_in is the list capacity).  accumulate != 0 keeps
 // max(previous, new) scores.  br.stats, given to a call's last launch: the order
@@ -41,6 +42,12 @@ hipError_t launch_proxy(int dtype, int qbits, const void *x_all, int B_all, int 
                         int d, int f, int group, int k_in, const void *blob,
                         uint8_t *in_mask, float *scores, int accumulate, Select sel, int act,
                         ScoreBracket br, hipStream_t stream);
+
+// The same for INT4 proxies (nb <= proxy_max_nb(d)).
+hipError_t launch_proxy_small(int dtype, const void *x_all, int B_all, int row0, int nb, int d,
+                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
+                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                              hipStream_t stream);
 
 // Stage 1 on the matrix cores for INT4 proxies: batch rows [row0, row0 + nb)
 // with nb <= proxy_mfma_rows(d, group, k_in) (16, 8, or 0 when the kept-row
@@ -54,8 +61,8 @@ hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, 
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                              int32_t *klist, int list_mode, hipStream_t stream);
-// Batch rows from which Stage 1 uses the matrix cores: 3 up to d_model 4096,
-// 5 above (where its 2-byte code loads keep too few bytes in flight).
+// Batch rows from which prox_stage1_mfma_rows reports that kernel: 3 up to d_model
+// 4096, 5 above.  (Calls of up to proxy_max_nb rows take launch_proxy_small.)
 inline int proxy_mfma_min_rows(int d) { return d <= 4096 ? 3 : 5; }
 
 // The three matrices of Stage 2: channel-major 16-bit rows (wq == 16), or

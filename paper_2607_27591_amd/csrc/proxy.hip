@@ -11,47 +11,17 @@
 // padded per quantisation group to an even count.  Each lane group then
 // streams a contiguous range of row pairs.
 //
-// A lane reads 8 (INT4), 8 or 16 (INT8) or 16 (unquantised 16-bit proxy)
-// bytes of both rows' contiguous segments, i.e. the same proxy columns of two
-// input rows.  INT4 codes are dequantised in fp16 whatever the model dtype:
-// byte k of both rows goes side by side (one v_perm), its low nibble OR-ed
-// under the exponent of 1024.0 is the exact fp16 pair (1024 + n_a, 1024 + n_b),
-// n = q + 8, and its high nibble in place, with the same OR, is
-// (1024 + 16 n_a, 1024 + 16 n_b); one v_dot2_f32_f16 each accumulates
-// x_a (...) + x_b (...) in fp32.  Both nibbles of a byte need no shift, which
-// bf16 (7 mantissa bits) would.  The kept x go to the list in fp16: bf16 x are
-// scaled by one power of two 2^s that puts the largest |x| in [2^14, 2^15), so
-// every kept x is exact in fp16 down to 2^-28 of the largest, and the sums are
-// scaled back by 2^-s.  The code bias ((1024 + 8) or (1024 + 128) times sum(x))
-// is subtracted and the group's scale applied once per group, column and lane
-// group; high-nibble columns are divided by 16 at the end.  Lane groups and waves are summed in a fixed order, so results are
-// deterministic.  This kernel takes up to 4 batch rows per launch; five or
-// more rows with an INT4 proxy go to proxy_mfma_kernel (the matrix cores).
+// A lane reads 8 (INT8) or 16 (unquantised 16-bit proxy) bytes of both rows'
+// contiguous segments, i.e. the same 8 proxy columns of two input rows.  The code
+// bias (128 times sum(x)) is subtracted and the group's scale applied once per
+// group, column and lane group.  Lane groups and waves are summed in a fixed
+// order, so results are deterministic.  Up to 4 batch rows per launch; INT4
+// proxies have kernels of their own (proxy_small_kernel, proxy_mfma_kernel).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"
 
 namespace prox {
-
-// acc[c] += x_a (1024 + n_a[c]) + x_b (1024 + n_b[c]) (even c) or
-// x_a (1024 + 16 n_a[c]) + x_b (1024 + 16 n_b[c]) (odd c) for the 8 INT4
-// columns of one 32-bit word of each row, x fp16: byte k of both words side by
-// side, then its low nibble (column 2k) or its high nibble in place (column
-// 2k + 1) OR-ed under the exponent of 1024.0, each exact in fp16.
-template <bool FUSED>
-__device__ __forceinline__ void int4_pair_dot8_h(uint32_t a, uint32_t b, uint32_t xpair,
-                                                 float *acc) {
-    constexpr uint32_t M = Int4Magic<kF16>::pair;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t p = __builtin_amdgcn_perm(b, a, (uint32_t)k | ((uint32_t)(k + 4) << 16));
-        acc[2 * k] = dot2<kF16>(xpair, and_or<FUSED>(p, 0x000F000Fu, M), acc[2 * k]);
-        acc[2 * k + 1] = dot2<kF16>(xpair, and_or<FUSED>(p, 0x00F000F0u, M), acc[2 * k + 1]);
-    }
-}
-// Code bias of column e of an fp16-dequantised INT4 word, and its scale.
-constexpr float kInt4HBias[2] = {1024.0f + 8.0f, 1024.0f + 128.0f};
-constexpr float kInt4HScale[2] = {1.0f, 1.0f / 16.0f};
 
 // acc[c] += x_a n_a[c] + x_b n_b[c] for 8 INT8 columns (n = q + 128).
 template <int DT>
@@ -87,36 +57,18 @@ __host__ __device__ inline size_t proxy_lds_bytes(int k_in, int ng, int nbt, int
     return m > kSelHistU16Bytes ? m : kSelHistU16Bytes;   // the selection's histogram first
 }
 
-// Columns each lane accumulates: 16 for one batch row of INT4 codes, else 8
-// (register budget).
-template <int NB>
-struct ProxyCols {
-    static constexpr int value = NB == 1 ? 16 : 8;
-};
-template <int NB, int QB>
-constexpr int proxy_cols() { return QB == 4 ? ProxyCols<NB>::value : 8; }
+constexpr int kProxyCols = 8;   // columns each lane accumulates
 
-template <int QB, int CPL>
+template <int QB>
 struct ProxyLoad;   // bytes of one row a lane reads
-template <> struct ProxyLoad<4, 16> { using type = uint2; };
-template <> struct ProxyLoad<4, 8> { using type = uint32_t; };
-template <> struct ProxyLoad<8, 16> { using type = uint4; };
-template <> struct ProxyLoad<8, 8> { using type = uint2; };
-template <> struct ProxyLoad<16, 8> { using type = uint4; };   // unquantised 16-bit proxy
+template <> struct ProxyLoad<8> { using type = uint2; };
+template <> struct ProxyLoad<16> { using type = uint4; };   // unquantised 16-bit proxy
 
-template <int DT, int QB, int CPL, bool FUSED>
-__device__ __forceinline__ void pair_accumulate(const typename ProxyLoad<QB, CPL>::type &a,
-                                                const typename ProxyLoad<QB, CPL>::type &b,
+template <int DT, int QB>
+__device__ __forceinline__ void pair_accumulate(const typename ProxyLoad<QB>::type &a,
+                                                const typename ProxyLoad<QB>::type &b,
                                                 uint32_t xp, float *acc) {
-    if constexpr (QB == 4 && CPL == 16) {
-        int4_pair_dot8_h<FUSED>(a.x, b.x, xp, acc);
-        int4_pair_dot8_h<FUSED>(a.y, b.y, xp, acc + 8);
-    } else if constexpr (QB == 4) {
-        int4_pair_dot8_h<FUSED>(a, b, xp, acc);
-    } else if constexpr (QB == 8 && CPL == 16) {
-        int8_pair_fma8<DT>(make_uint2(a.x, a.y), make_uint2(b.x, b.y), xp, acc);
-        int8_pair_fma8<DT>(make_uint2(a.z, a.w), make_uint2(b.z, b.w), xp, acc + 8);
-    } else if constexpr (QB == 8) {
+    if constexpr (QB == 8) {
         int8_pair_fma8<DT>(a, b, xp, acc);
     } else {
         // 16-bit weights: (w_a[c], w_b[c]) side by side, one dot2 with (x_a, x_b).
@@ -136,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
     int d, int f, int group, int k_in, const uint8_t *__restrict__ blob,
     uint8_t *__restrict__ in_mask, float *__restrict__ scores,
     int accumulate, Select sel_rule, int act, ScoreBracket br) {   // k_in: the list capacity when sel_rule.tau_mode
-    constexpr int CPL = proxy_cols<NB, QB>();
+    constexpr int CPL = kProxyCols;
     constexpr int LPS = 2 * T / CPL;              // lanes per row segment (gate + up)
     constexpr int NGRP = kWave / LPS;             // lane groups per wave
     constexpr int NLG = kMaxBlockWaves * NGRP;    // lane groups per workgroup
@@ -145,9 +97,8 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
     constexpr int SZ = CPL / 8;                   // uint4 of scales per lane and group
     constexpr bool kEarlyX = NB <= 2;             // projected x loaded with the keys
     constexpr bool kHoistX = NB == 1;             // x pairs read with the code loads
-    constexpr float off = QB == 8 ? 128.0f : 0.0f;   // code bias (INT4: per column, kInt4HBias)
-    constexpr bool kHx = QB == 4;                     // x in fp16 (INT4 codes dequantised in fp16)
-    using W = typename ProxyLoad<QB, CPL>::type;
+    constexpr float off = QB == 8 ? 128.0f : 0.0f;   // code bias
+    using W = typename ProxyLoad<QB>::type;
     const BlobLayout L(d, f, QB, group);
     const int tid = threadIdx.x, wid = tid / kWave, lane = lane_id();
     const int tile = stage1_tile<2 * T * QB / 8 < 128>(blockIdx.x, gridDim.x);
@@ -215,19 +166,6 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
             }
         }
     }
-    // bf16 x for fp16-dequantised codes: the largest key sets the power of two
-    // that takes the kept x into fp16 (per wave here, across waves after the
-    // bookkeeping barrier; 15-bit magnitude patterns order like the values).
-    constexpr bool kScaleX = kHx && DT == kBF16;
-    __shared__ uint32_t wmax[kMaxBlockWaves];
-    if constexpr (kScaleX) {
-        uint32_t m = 0;
-#pragma unroll
-        for (int r = 0; r < C; ++r) m = max(m, key[r]);
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-        if (lane == 0) wmax[wid] = m;
-    }
     uint64_t sel = 0;
     if (sel_rule.tau_mode) {
         // Threshold rule: keep row i when max_b |x_{b,i}| >= tau_x, compared
@@ -290,16 +228,6 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
         }
     }
 
-    float xscale = 1.0f, xunscale = 1.0f;   // 2^s and 2^-s (bf16 x to fp16)
-    if constexpr (kScaleX) {
-        uint32_t m = 0;
-#pragma unroll
-        for (int w = 0; w < kMaxBlockWaves; ++w) m = max(m, wmax[w]);
-        const int sx = min(100, max(-100, 141 - (int)(m >> 7)));   // 2^14 <= max |x| 2^s < 2^15
-        xscale = __uint_as_float((uint32_t)(127 + sx) << 23);
-        xunscale = __uint_as_float((uint32_t)(127 - sx) << 23);
-    }
-
     // ---- kept rows to their padded list positions (x as 16-bit bits) ----
     // A kept input's position: its entry's first position plus its rank in
     // the entry (a lane count).
@@ -331,9 +259,7 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
 #pragma unroll
         for (int r = 0; r < C; ++r) {
             if (pos[r] >= 0) {
-                uint16_t v = b < nb ? xv[r] : (uint16_t)0;
-                if constexpr (kScaleX) v = float_to_f16_rne(bf16_lo(v) * xscale);   // exact above 2^-28 of the largest
-                xs_sh[b * cap + pos[r]] = v;
+                xs_sh[b * cap + pos[r]] = b < nb ? xv[r] : (uint16_t)0;
             }
         }
     }
@@ -354,8 +280,8 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
     }
 
     // ---- stream the kept row pairs: lane group l owns a contiguous range ----
-    // Per group the lane accumulates x_a (M + n_a) + x_b (M + n_b) and the x
-    // sum; at a group change acc - (M + 8) * xsum is scaled into tot.
+    // Per group the lane accumulates x_a n_a + x_b n_b (n = q + 128 for INT8) and
+    // the x sum; at a group change acc - 128 * xsum is scaled into tot.
     const int npairs = gstart[ng] / 2;
     const int lgi = wid * NGRP + lane / LPS;
     const int pa = (int)((long long)lgi * npairs / NLG);
@@ -402,8 +328,7 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
                     const float sg = f16_bits_to_float((e & 1) ? (sw[e >> 1] >> 16) : (sw[e >> 1] & 0xFFFFu));
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
-                        const float offe = kHx ? kInt4HBias[e & 1] : off;
-                        tot[b][z * 8 + e] = fmaf(sg, acc[b][z * 8 + e] - offe * xs[b], tot[b][z * 8 + e]);
+                        tot[b][z * 8 + e] = fmaf(sg, acc[b][z * 8 + e] - off * xs[b], tot[b][z * 8 + e]);
                         acc[b][z * 8 + e] = 0.0f;
                     }
                 }
@@ -441,22 +366,14 @@ __global__ __launch_bounds__(kBlock) void proxy_kernel(
                         uint32_t xp;
                         if constexpr (kHoistX) xp = p < pb ? xpre[u] : 0u;
                         else xp = p < pb ? xs32[b * (cap / 2) + p] : 0u;
-                        pair_accumulate<DT, QB, CPL, (NB <= 2)>(wa[u], wb[u], xp, acc[b]);
-                        if constexpr (kHx) xs[b] = dot2<kF16>(xp, Int4Magic<kF16>::one, xs[b]);
-                        else xs[b] = dot2<DT>(xp, Int4Magic<DT>::one, xs[b]);
+                        pair_accumulate<DT, QB>(wa[u], wb[u], xp, acc[b]);
+                        xs[b] = dot2<DT>(xp, Int4Magic<DT>::one, xs[b]);
                     }
                 }
             }
         }
         flush();
     }
-    if constexpr (kHx) {   // high-nibble columns / 16, and 2^-s: exact powers of two
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int e = 0; e < CPL; ++e) tot[b][e] *= kInt4HScale[e & 1] * xunscale;
-    }
-
     // ---- combine lane groups, then waves, in a fixed order ----
     static_assert(LPS == 8 || LPS == 16 || LPS == 32, "lane-group sizes");
 #pragma unroll
@@ -565,8 +482,9 @@ hipError_t launch_proxy(int dtype, int qbits, const void *x_all, int B_all, int 
                         int d, int f, int group, int k_in, const void *blob,
                         uint8_t *in_mask, float *scores, int accumulate, Select sel_rule, int act, ScoreBracket br, hipStream_t s) {
 #define PX(DT_, QB_) launch_proxy_tile<DT_, QB_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel_rule, act, br, s)
-    if (dtype == kBF16) return qbits == 4 ? PX(kBF16, 4) : qbits == 8 ? PX(kBF16, 8) : PX(kBF16, 16);
-    return qbits == 4 ? PX(kF16, 4) : qbits == 8 ? PX(kF16, 8) : PX(kF16, 16);
+    if (qbits == 4) return hipErrorInvalidValue;   // launch_proxy_small, launch_proxy_mfma
+    if (dtype == kBF16) return qbits == 8 ? PX(kBF16, 8) : PX(kBF16, 16);
+    return qbits == 8 ? PX(kF16, 8) : PX(kF16, 16);
 #undef PX
 }
 

@@ -316,6 +316,24 @@ __device__ __forceinline__ void narrow_pass(const uint32_t (&key)[C], int n, int
     find_digit<NBINS, false>(h, kk, ss, digit, kk, bucket);
 }
 
+// The k-th largest v of 15-bit keys, items owned strided; `need` of its `bucket`
+// equal keys are in (need = bucket: v may be a bin's lower edge).  Bits 14..3,
+// then 2..0, over 4096- and 8-bin histograms: the first pass takes mantissa bits
+// as well as the exponent, as keys crowd into a few exponents and same-word LDS
+// atomics serialise.  hist: 4096 + 8 words of LDS, zeroed, the zeros visible.
+template <int C>
+__device__ __forceinline__ void kth_magnitude(const uint32_t (&key)[C], int n, int k, uint32_t *hist,
+                                              SelScratch &ss, uint32_t &v, int &need, int &bucket) {
+    uint32_t d1, d2;
+    need = k;
+    narrow_pass<C, 4096>(key, n, threadIdx.x, kBlock, 3, 0, hist, ss, need, bucket, d1);
+    v = d1 << 3;
+    if (need < bucket) {
+        narrow_pass<C, 8>(key, n, threadIdx.x, kBlock, 0, d1, hist + 4096, ss, need, bucket, d2);
+        v |= d2;
+    }
+}
+
 // Top k (1 <= k <= n) of 15-bit keys (magnitude patterns of 16-bit floats):
 // one histogram pass over all 2^15 values finds the k-th largest key v; ties
 // at v are cut by index.  hist: kSelHistU16Words words of LDS.  Fills ord.
@@ -326,24 +344,16 @@ __device__ __forceinline__ void topk_select_u15(const uint32_t (&key)[C], int n,
     static_assert(C * NT < 65536, "a 16-bit counter holds every key");
     const int tid = threadIdx.x;
     if constexpr (C * NT <= 4096) {
-        // Few keys: bits 14..3, then 2..0, over 4096- and 8-bin histograms.
-        // The first pass takes mantissa bits as well as the exponent: keys
-        // crowd into a few exponents, and same-word LDS atomics serialise.
-        uint32_t *h1 = hist, *h2 = hist + 4096;
+        // Few keys: two narrow passes.
         for (int i = tid; i < (4096 + 8) / 4; i += NT)
             reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
         __syncthreads();
-        int kk = k, bucket;
-        uint32_t d1, d2;
-        narrow_pass<C, 4096>(key, n, tid, NT, 3, 0, h1, ss, kk, bucket, d1);
-        uint32_t v = d1 << 3;
-        if (kk < bucket) {
-            narrow_pass<C, 8>(key, n, tid, NT, 0, d1, h2, ss, kk, bucket, d2);
-            v = (d1 << 3) | d2;
-            if (kk < bucket) {
-                topk_table_cut<NT, C>(key, n, v, kk, hist, ord);
-                return;
-            }
+        uint32_t v;
+        int need, bucket;
+        kth_magnitude<C>(key, n, k, hist, ss, v, need, bucket);
+        if (need < bucket) {
+            topk_table_cut<NT, C>(key, n, v, need, hist, ord);
+            return;
         }
         topk_table<NT, C>(key, n, v, ord);
         return;

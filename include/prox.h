@@ -64,9 +64,10 @@ typedef enum PROX_ENUM_INT { PROX_ACT_SILU = 0, PROX_ACT_GELU = 1 } prox_act;
 typedef enum PROX_ENUM_INT { PROX_Q_INT8 = 0, PROX_Q_INT4 = 1, PROX_Q_NONE = 2 } prox_qfmt;
 
 /* Supported sizes.  Batches past the rows one launch takes (Stage 1: 4 on the
- * dot-product and small-batch kernels, 8 or 16 on the matrix cores; Stage 2: every row on the
- * matrix-core path, see prox_stage2_rows, else 8, fewer for INT4 base
- * weights on wide d_model) run as several launches on the same stream:
+ * dot-product kernel, 8 or 16 on the 16-row matrix-core kernel, every row on
+ * the batch kernels; Stage 2: every row on the matrix-core path, see
+ * prox_stage2_rows, else 8, fewer for INT4 base weights on wide d_model) run
+ * as several launches on the same stream:
  * Stage 1 takes the max of the scores over them, Stage 2 writes disjoint rows
  * of the partial sums, so the result does not depend on the split.  Each
  * Stage 2 launch reads the kept rows again. */
@@ -144,15 +145,16 @@ prox_status prox_unpack_proxy(const prox_proxy *p, int d_model, int d_ff, int8_t
 size_t prox_workspace_bytes(int d_model, int d_ff, int batch);
 
 /*
- * How Stage 1 covers a batch (for inspection and tests): the batch rows one
- * launch of the 16-row matrix-core kernel covers for this shape, or 0 (an INT8
- * or unquantised proxy, fewer than three batch rows up to d_model 4096 or fewer
- * than five above, a kept-input list too long for the LDS, or an unsupported
- * shape).  Calls of up to four rows with an INT4 proxy (one above d_model 8192)
- * run on the small-batch kernel whatever is reported, and those with 0 in
- * several launches of it.  k_in is the kept-input count; the threshold entry
- * point sizes its list for k_in = d_model.  Host only, no HIP calls.  The
- * kernels compute the same proxy in a different fp32 summation order.
+ * Batch rows one launch of the 16-row matrix-core Stage-1 kernel can cover for
+ * this shape (for inspection and tests), or 0 (an INT8 or unquantised proxy,
+ * fewer than three batch rows up to d_model 4096 or fewer than five above, a
+ * kept-input list too long for the LDS, or an unsupported shape).  Calls with
+ * an INT4 proxy take that kernel for 5 to 16 rows up to d_model 4096, the
+ * small-batch kernel for fewer rows (one above d_model 8192), and else the
+ * batch kernels, which select once for every row.  k_in is the kept-input
+ * count; the threshold entry point sizes its list for k_in = d_model.  Host
+ * only, no HIP calls.  The kernels compute the same proxy in a different fp32
+ * summation order.
  */
 int prox_stage1_mfma_rows(int d_model, prox_qfmt fmt, int group, int batch, int k_in);
 

@@ -158,6 +158,21 @@ int stage1_mfma_rows(int d, int qbits, int group, int batch, int k_in) {
     return qbits == 4 && batch >= proxy_mfma_min_rows(d) ? proxy_mfma_rows(d, group, k_in) : 0;
 }
 
+// Stage 1 kernels of a call.  INT4 proxies: up to four rows (one above d = 8192) on
+// the small-batch kernel (4096 x 14336, four rows: the call takes 54 us, 57 on the
+// 16-row matrix-core kernel); up to 16 rows at d <= 4096 on that kernel (16 rows:
+// one launch of 23 us, where the batch kernels' three take 31); the rest on the
+// batch kernels, which select once for all rows (the call at 8192 x 14336: 12 rows 94.5
+// us, 129.8 in two launches of 8 rows; 6 rows 110.6, 113.5 in one).  The same for
+// both selection rules, so that equal sets give equal bits.  INT8 and unquantised
+// proxies: the dot-product kernel.
+enum Stage1Route { kStage1Dot, kStage1Small, kStage1Mfma, kStage1Batch };
+Stage1Route stage1_route(int d, int qbits, int batch) {
+    if (qbits != 4) return kStage1Dot;
+    if (batch <= proxy_max_nb(d)) return kStage1Small;
+    return d <= 4096 && batch <= 16 ? kStage1Mfma : kStage1Batch;
+}
+
 // The bracket of a top-k call's channel selection (ScoreBracket).  Its order
 // statistics go to the end of the kept-list area, [f - 2 n, f), which a call
 // that keeps k_ff <= f - 2 n channels never writes: the list takes [0, k_ff) and
@@ -225,35 +240,34 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
     const Ws W = carve(ws, d, f, batch, m.s2.wq);
     const int dt = m.dtype;
     if (events) PROX_TRY(hipEventRecord(events[0], stream));
-    // INT4 proxies: up to four rows (one above d = 8192) on the small-batch kernel,
-    // more on the 16-row matrix-core kernel, which reads the codes once for up to
-    // 16 rows (at 4096 x 14336 and four rows 54.1 us the call, 56.8 on that one), or
-    // in several small-batch launches where its list does not fit.  INT8 and
-    // unquantised proxies: the dot-product kernel.
-    const int mfma_rows = batch <= proxy_max_nb(d) ? 0 : stage1_mfma_rows(d, qbits, p->group, batch, k_in);
-    const int pnb = mfma_rows ? mfma_rows : proxy_max_nb(d);
     const ScoreBracket br = score_bracket(f, k_ff, W.klist);
-    for (int c0 = 0; c0 < batch; c0 += pnb) {
-        const int nb = batch - c0 < pnb ? batch - c0 : pnb;
-        const ScoreBracket out = c0 + pnb >= batch ? br : ScoreBracket{};
-        const Select in_sel{rules.tau_mode, rules.tau_x, rules.counts};
-        // With several matrix-core launches only the first selects; its list
-        // of kept rows goes to the partial-y area, which Stage 2 writes only
-        // after the last Stage 1 launch.
-        const int list_mode = batch <= pnb ? kListNone : c0 == 0 ? kListWrite : kListRead;
-        if (mfma_rows)
-            PROX_TRY(launch_proxy_mfma(dt, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
-                                       c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel,
-                                       m.act, out, reinterpret_cast<int32_t *>(W.ypart), list_mode,
-                                       stream));
-        else if (qbits == 4)
-            PROX_TRY(launch_proxy_small(dt, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
-                                        c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel, m.act,
-                                        out, stream));
-        else
-            PROX_TRY(launch_proxy(dt, qbits, x, batch, c0, nb, d, f, p->group, k_in, p->blob,
-                                  c0 == 0 ? in_mask : nullptr, W.scores, c0 > 0, in_sel, m.act,
-                                  out, stream));
+    const Select in_sel{rules.tau_mode, rules.tau_x, rules.counts};
+    const int route = stage1_route(d, qbits, batch);
+    if (route == kStage1Batch) {
+        // Scratch: the partial-y area, which Stage 2 writes only afterwards.
+        PROX_TRY(launch_proxy_batch(dt, x, batch, d, f, p->group, k_in, p->blob, in_mask, W.scores,
+                                    in_sel, m.act, br, W.ypart, stream));
+    } else {
+        const int pnb = route == kStage1Mfma ? proxy_mfma_rows(d, p->group, k_in) : proxy_max_nb(d);
+        for (int c0 = 0; c0 < batch; c0 += pnb) {
+            const int nb = batch - c0 < pnb ? batch - c0 : pnb;
+            const ScoreBracket out = c0 + pnb >= batch ? br : ScoreBracket{};
+            uint8_t *im = c0 == 0 ? in_mask : nullptr;
+            // With several matrix-core launches (the threshold rule's longer list)
+            // only the first selects; its list of kept rows goes to the partial-y
+            // area as well.
+            const int list_mode = batch <= pnb ? kListNone : c0 == 0 ? kListWrite : kListRead;
+            if (route == kStage1Mfma)
+                PROX_TRY(launch_proxy_mfma(dt, x, batch, c0, nb, d, f, p->group, k_in, p->blob, im,
+                                           W.scores, c0 > 0, in_sel, m.act, out,
+                                           reinterpret_cast<int32_t *>(W.ypart), list_mode, stream));
+            else if (route == kStage1Small)
+                PROX_TRY(launch_proxy_small(dt, x, nb, d, f, p->group, k_in, p->blob, im, W.scores,
+                                            in_sel, m.act, out, stream));
+            else
+                PROX_TRY(launch_proxy(dt, qbits, x, batch, c0, nb, d, f, p->group, k_in, p->blob, im,
+                                      W.scores, c0 > 0, in_sel, m.act, out, stream));
+        }
     }
     if (events) PROX_TRY(hipEventRecord(events[1], stream));
     const Select ff_sel{rules.tau_mode, rules.tau_s, rules.counts ? rules.counts + 1 : nullptr};

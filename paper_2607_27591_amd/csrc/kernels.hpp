@@ -43,13 +43,19 @@ hipError_t launch_proxy(int dtype, int qbits, const void *x_all, int B_all, int 
                         uint8_t *in_mask, float *scores, int accumulate, Select sel, int act,
                         ScoreBracket br, hipStream_t stream);
 
-// The same for INT4 proxies (nb <= proxy_max_nb(d)).
-hipError_t launch_proxy_small(int dtype, const void *x_all, int B_all, int row0, int nb, int d,
-                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
-                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
-                              hipStream_t stream);
+// The same for INT4 proxies, all rows of a call (nb <= proxy_max_nb(d)).
+hipError_t launch_proxy_small(int dtype, const void *x, int nb, int d, int f, int group, int k_in,
+                              const void *blob, uint8_t *in_mask, float *scores, Select sel, int act,
+                              ScoreBracket br, hipStream_t stream);
 
-// Stage 1 on the matrix cores for INT4 proxies: batch rows [row0, row0 + nb)
+// The same for every row of a batch in three launches that select once; scratch:
+// proxy_batch_scratch_bytes(d, group, batch) bytes, 256-byte aligned.
+size_t proxy_batch_scratch_bytes(int d, int group, int batch);
+hipError_t launch_proxy_batch(int dtype, const void *x, int batch, int d, int f, int group, int k_in,
+                              const void *blob, uint8_t *in_mask, float *scores, Select sel, int act,
+                              ScoreBracket br, void *scratch, hipStream_t stream);
+
+// Stage 1 on the matrix cores for INT4 proxies and d <= 4096: batch rows [row0, row0 + nb)
 // with nb <= proxy_mfma_rows(d, group, k_in) (16, 8, or 0 when the kept-row
 // list does not fit in LDS); otherwise as launch_proxy.
 int proxy_mfma_rows(int d, int group, int k_in);
@@ -62,7 +68,7 @@ hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, 
                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                              int32_t *klist, int list_mode, hipStream_t stream);
 // Batch rows from which prox_stage1_mfma_rows reports that kernel: 3 up to d_model
-// 4096, 5 above.  (Calls of up to proxy_max_nb rows take launch_proxy_small.)
+// 4096, 5 above.  (Which kernel a call takes: stage1_route.)
 inline int proxy_mfma_min_rows(int d) { return d <= 4096 ? 3 : 5; }
 
 // The three matrices of Stage 2: channel-major 16-bit rows (wq == 16), or

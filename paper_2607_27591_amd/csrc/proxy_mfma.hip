@@ -1,8 +1,8 @@
 // Stage 1 of the sparse decode step for several batch rows at once, on the
 // matrix cores (Sec. 4.1 Stage 1 with the INT4 proxy of Sec. 3.2 / 4.3).  It
-// computes what proxy_kernel computes (the same input selection, the same
-// per-group scales and the same score) for up to 16 rows per launch, so the
-// proxy codes of a kept input row are read once for all of them.
+// computes the proxy and the score as proxy.hip states them for up to 16 rows per
+// launch (5 to 16 rows at d_model up to 4096), so the proxy codes of a kept input
+// row are read once for all of them.
 //
 // The proxy GEMV of a column tile is a product of x (batch rows x kept input
 // rows) with the dequantised codes (kept input rows x columns), done as
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
             for (int b = 0; b < nb; ++b) xs_sh[(size_t)p * NX + b] = x_all[(size_t)(row0 + b) * d + i];
         }
     } else {
-        // ---- input selection (as proxy_kernel): key = max_b |x_{b,i}| bits ----
+        // ---- input selection: key = max_b |x_{b,i}| bits ----
         // x is read XQ rows at a time, two rows' 16-bit values per register,
         // so a round's loads are in flight together (XQ * C = 64 values in 32
         // registers per thread: one round trip for 16 rows of d <= 4096; two
@@ -432,9 +432,7 @@ static hipError_t launch_mfma_c(const void *x_all, int B_all, int row0, int nb, 
                                 int32_t *klist, int list_mode, hipStream_t s) {
     const int nx = proxy_mfma_rows(d, group, k_in);
 #define MF(C_, NX_) launch_mfma_t<DT, T, C_, NX_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
-    if (d <= 4 * kBlock) return nx == 16 ? MF(4, 16) : MF(4, 8);
-    if (d <= 8 * kBlock) return nx == 16 ? MF(8, 16) : MF(8, 8);
-    return nx == 16 ? MF(16, 16) : MF(16, 8);
+    return nx == 16 ? MF(4, 16) : MF(4, 8);
 #undef MF
 }
 
@@ -442,7 +440,8 @@ hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, 
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                              int32_t *klist, int list_mode, hipStream_t s) {
-    if (nb < 1 || nb > proxy_mfma_rows(d, group, k_in)) return hipErrorInvalidValue;
+    // Wider d takes the batch kernels: 4 input rows per thread here.
+    if (nb < 1 || d > 4 * kBlock || nb > proxy_mfma_rows(d, group, k_in)) return hipErrorInvalidValue;
     if (list_mode != kListNone && !klist) return hipErrorInvalidValue;
     if (proxy_tile(f) == 128)
         return dtype == kBF16 ? launch_mfma_c<kBF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)

@@ -57,9 +57,9 @@ __host__ __device__ constexpr size_t proxy_small_lds_bytes(int NB, int T, int C)
 
 template <int NB, int DT, int T, int C>
 __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
-    const uint16_t *__restrict__ x_all, int B_all, int row0, int nb, int d, int f, int group, int k_in,
+    const uint16_t *__restrict__ x, int nb, int d, int f, int group, int k_in,
     const uint8_t *__restrict__ blob, uint8_t *__restrict__ in_mask, float *__restrict__ scores,
-    int accumulate, Select sel_rule, int act, ScoreBracket br) {
+    Select sel_rule, int act, ScoreBracket br) {
     constexpr int CPL = 8;                  // columns per lane
     constexpr int LPS = 2 * T / CPL;        // lanes per row segment (gate, then up)
     constexpr int NGRP = kWave / LPS;       // lane groups per wave: 4 or 2
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
     // x of the projected rows stays in registers, two inputs per word.
     uint32_t key[C], xw[NB][C / 2];
     {
-        const auto rx = buffer_of(x_all, (uint32_t)(B_all * d) * 2);
+        const auto rx = buffer_of(x, (uint32_t)(nb * d) * 2);
         auto load_row = [&](int b, uint32_t (&w)[C / 2]) {   // inputs past d: 0
             const int base = b * d;
 #pragma unroll
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
             }
         };
 #pragma unroll
-        for (int b = 0; b < NB; ++b) load_row(row0 + min(b, nb - 1), xw[b]);
+        for (int b = 0; b < NB; ++b) load_row(min(b, nb - 1), xw[b]);
         for (int i = tid; i < kSmallHistWords / 4; i += kBlock)
             reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0, 0, 0, 0);
 #pragma unroll
@@ -110,13 +110,6 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
 #pragma unroll
             for (int b = 0; b < NB; ++b) key[r] = max(key[r], (xw[b][r / 2] >> (16 * (r & 1))) & 0x7FFFu);
         }
-        if (B_all > nb)   // the selection ranks every row of the call
-            for (int b = 0; b < B_all; ++b) {
-                uint32_t w[C / 2];
-                load_row(b, w);
-#pragma unroll
-                for (int r = 0; r < C; ++r) key[r] = max(key[r], (w[r / 2] >> (16 * (r & 1))) & 0x7FFFu);
-            }
     }
     // The threshold rule's kept count, for what follows to be that of a top-k call
     // with this count (the order of the lists, and so the sums' bits).
@@ -133,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
     if (sel_rule.tau_mode) {
         k_in = __builtin_amdgcn_readlane(
             wave_inclusive_scan(lane < kMaxBlockWaves ? kept_sh[lane] : 0), kMaxBlockWaves - 1);
-        if (tile == 0 && row0 == 0 && tid == 0 && sel_rule.count) *sel_rule.count = k_in;
+        if (tile == 0 && tid == 0 && sel_rule.count) *sel_rule.count = k_in;
     }
 
     // ---- this wave's surely kept inputs of its first blocks, loads on their way ----
@@ -454,10 +447,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
             }
             best = fmaxf(best, fabsf(gate_act(gu[0], act) * gu[1]));
         }
-        if (j < f) {
-            if (accumulate) best = fmaxf(scores[j], best);
-            scores[j] = best;
-        }
+        if (j < f) scores[j] = best;
         sc_tile[tid] = __float_as_uint(best);
     }
     if (br.stats && (tile + 1) * T <= f) {
@@ -467,9 +457,9 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
 }
 
 template <int NB, int DT, int T, int C>
-static hipError_t launch_small_t(const void *x_all, int B_all, int row0, int nb, int d, int f,
+static hipError_t launch_small_t(const void *x, int nb, int d, int f,
                                  int group, int k_in, const void *blob, uint8_t *in_mask,
-                                 float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                                 float *scores, Select sel, int act, ScoreBracket br,
                                  hipStream_t s) {
     const BlobLayout L(d, f, 4, group);
     constexpr size_t lds = proxy_small_lds_bytes(NB, T, C);
@@ -481,18 +471,18 @@ static hipError_t launch_small_t(const void *x_all, int B_all, int row0, int nb,
         if (e != hipSuccess) return e;
     }
     proxy_small_kernel<NB, DT, T, C><<<L.n_tiles, kBlock, lds, s>>>(
-        static_cast<const uint16_t *>(x_all), B_all, row0, nb, d, f, group, k_in,
-        static_cast<const uint8_t *>(blob), in_mask, scores, accumulate, sel, act, br);
+        static_cast<const uint16_t *>(x), nb, d, f, group, k_in,
+        static_cast<const uint8_t *>(blob), in_mask, scores, sel, act, br);
     return hipGetLastError();
 }
 
 // C = blocks per wave: 4 up to d = 4096, 8 up to 8192, else 16 (one batch row).
 template <int DT, int T>
-static hipError_t launch_small_c(const void *x_all, int B_all, int row0, int nb, int d, int f,
+static hipError_t launch_small_c(const void *x, int nb, int d, int f,
                                  int group, int k_in, const void *blob, uint8_t *in_mask,
-                                 float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                                 float *scores, Select sel, int act, ScoreBracket br,
                                  hipStream_t s) {
-#define SM(NB_, C_) return launch_small_t<NB_, DT, T, C_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, s)
+#define SM(NB_, C_) return launch_small_t<NB_, DT, T, C_>(x, nb, d, f, group, k_in, blob, in_mask, scores, sel, act, br, s)
     if (d <= 4 * kBlock) {
         if (nb == 1) SM(1, 4);
         if (nb == 2) SM(2, 4);
@@ -507,12 +497,12 @@ static hipError_t launch_small_c(const void *x_all, int B_all, int row0, int nb,
 #undef SM
 }
 
-hipError_t launch_proxy_small(int dtype, const void *x_all, int B_all, int row0, int nb, int d,
+hipError_t launch_proxy_small(int dtype, const void *x, int nb, int d,
                               int f, int group, int k_in, const void *blob, uint8_t *in_mask,
-                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
+                              float *scores, Select sel, int act, ScoreBracket br,
                               hipStream_t s) {
     if (nb < 1 || nb > proxy_max_nb(d)) return hipErrorInvalidValue;
-#define SM(DT_, T_) launch_small_c<DT_, T_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, s)
+#define SM(DT_, T_) launch_small_c<DT_, T_>(x, nb, d, f, group, k_in, blob, in_mask, scores, sel, act, br, s)
     if (proxy_tile(f) == 128) return dtype == kBF16 ? SM(kBF16, 128) : SM(kF16, 128);
     return dtype == kBF16 ? SM(kBF16, 64) : SM(kF16, 64);
 #undef SM

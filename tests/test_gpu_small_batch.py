@@ -1,8 +1,8 @@
-"""The small-batch Stage 1 where its lists can go wrong: every count of 64-input
-blocks per wave and of lane groups sharing them (d_model 128 to 16384, both tile
-widths), all inputs kept, one kept, clustered ones (some waves keep all of their
-inputs, others none, and the early guess misses) and tied magnitudes, against
-the oracle's selection and scores."""
+"""The small-batch and batch Stage 1 where their lists can go wrong: every count of
+64-input blocks per wave and of lane groups sharing them (d_model 128 to 16384, both
+tile widths), row tiles of 16, 32 and 64, all inputs kept, one kept, clustered ones
+(some waves keep all of their inputs, others none, and the early guess misses) and
+tied magnitudes, against the oracle's selection and scores."""
 import numpy as np
 import pytest
 import torch
@@ -33,7 +33,11 @@ def inputs(kind, batch, d, rng):
     (2176, 64, 4, 128, W.DT_BF16), (3200, 129, 3, 128, W.DT_F16), (4096, 64, 4, 128, W.DT_F16),
     (5120, 100, 1, 128, W.DT_BF16), (6272, 65, 4, 896, W.DT_BF16), (7296, 64, 2, 128, W.DT_F16),
     (8192, 130, 4, 128, W.DT_BF16), (16384, 64, 1, 128, W.DT_BF16), (16384, 70, 2, 128, W.DT_F16),
-    (256, 24500, 1, 128, W.DT_BF16), (1408, 24449, 4, 128, W.DT_F16)])
+    (256, 24500, 1, 128, W.DT_BF16), (1408, 24449, 4, 128, W.DT_F16),
+    # batch kernels
+    (128, 70, 17, 128, W.DT_BF16), (1152, 200, 32, 128, W.DT_F16), (4096, 65, 33, 256, W.DT_BF16),
+    (4224, 130, 5, 128, W.DT_F16), (8192, 64, 16, 8192, W.DT_BF16), (16384, 64, 3, 128, W.DT_F16),
+    (256, 24500, 20, 128, W.DT_F16), (384, 24449, 64, 128, W.DT_BF16)])
 def test_scores_and_input_mask(d, f, batch, group, dtype, kind):
     rng = np.random.default_rng(d + f + batch)
     bits = [W.to_bits((rng.standard_normal((f, d)) * 0.02).astype(np.float32), dtype) for _ in range(2)]

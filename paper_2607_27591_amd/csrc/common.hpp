@@ -131,22 +131,25 @@ __device__ __forceinline__ uint2 load_stream8(const void *p) {
 }
 
 // Bounds-checked loads from [p, p + bytes): past the end they return 0, at no
-// instruction's cost.  off: per lane, imm: a constant, both in bytes.
+// instruction's cost.  off: per lane, in bytes.  The whole offset is the per-lane
+// one (the compiler moves up to 4095 of it into the instruction): these two are
+// what the range check covers, while the scalar offset is left out of it by the
+// intrinsics' description and stays 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }
-__device__ __forceinline__ uint32_t buffer_load32(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
-    return __builtin_amdgcn_raw_buffer_load_b32(rs, off + (imm & 4095), imm & ~4095, 0);
+__device__ __forceinline__ uint32_t buffer_load32(__amdgpu_buffer_rsrc_t rs, int off) {
+    return __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
 }
-__device__ __forceinline__ uint32_t buffer_load16(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
-    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off + (imm & 4095), imm & ~4095, 0);
+__device__ __forceinline__ uint32_t buffer_load16(__amdgpu_buffer_rsrc_t rs, int off) {
+    return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
 }
-__device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off + (imm & 4095), imm & ~4095, 0);
+__device__ __forceinline__ uint2 buffer_load64(__amdgpu_buffer_rsrc_t rs, int off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
     return make_uint2(v[0], v[1]);
 }
-__device__ __forceinline__ uint4 buffer_load128(__amdgpu_buffer_rsrc_t rs, int off, int imm) {
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, off + (imm & 4095), imm & ~4095, 0);
+__device__ __forceinline__ uint4 buffer_load128(__amdgpu_buffer_rsrc_t rs, int off) {
+    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 

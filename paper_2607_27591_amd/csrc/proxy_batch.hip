@@ -53,7 +53,7 @@ __global__ __launch_bounds__(256) void proxy_keys_kernel(const uint16_t *__restr
     const int off = (blockIdx.x * 128 + 2 * l) * 2;
     uint32_t v[16], lo = 0, hi = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) v[q] = buffer_load32(rx, off + (g + 4 * q) * d * 2, 0);
+    for (int q = 0; q < 16; ++q) v[q] = buffer_load32(rx, off + (g + 4 * q) * d * 2);
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         lo = max(lo, v[q] & 0x7FFFu);
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
     uint32_t key[C];
     const auto rk = buffer_of(keys, (uint32_t)d * 4);   // past d: 0
 #pragma unroll
-    for (int r = 0; r < C; ++r) key[r] = buffer_load32(rk, tid * 4, r * kBlock * 4);
+    for (int r = 0; r < C; ++r) key[r] = buffer_load32(rk, (r * kBlock + tid) * 4);
     if (sel_rule.tau_mode) {
         uint64_t sel = 0;
 #pragma unroll

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const int i = (2 * q + e) * kBlock + tid;
-                    h[e] = buffer_load16(rx, i < d ? (base + i) * 2 : 0x7FFFFFFF, 0);
+                    h[e] = buffer_load16(rx, i < d ? (base + i) * 2 : 0x7FFFFFFF);
                 }
                 w[q] = h[0] | (h[1] << 16);
             }

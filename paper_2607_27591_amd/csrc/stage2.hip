@@ -131,7 +131,7 @@ __device__ __forceinline__ int stage2_slice(const float *__restrict__ scores, in
         uint32_t key[C];
         const auto rs = buffer_of(scores, (uint32_t)f * 4);
 #pragma unroll
-        for (int r = 0; r < C; ++r) key[r] = buffer_load32(rs, first * 4, r * kWave * 4);
+        for (int r = 0; r < C; ++r) key[r] = buffer_load32(rs, (first + r * kWave) * 4);
         uint32_t v = 0, top = 0x7FFFFFFFu;   // kept: v <= key <= top, when `plain`
         int need = 0, bucket = 0;
         if (sel_rule.tau_mode) {
@@ -146,7 +146,7 @@ __device__ __forceinline__ int stage2_slice(const float *__restrict__ scores, in
                 uint2 e[NS];
                 const auto bs = buffer_of(br.stats, (uint32_t)br.n * 8);
 #pragma unroll
-                for (int t = 0; t < NS; ++t) e[t] = buffer_load64(bs, lane * 8, t * kWave * 8);
+                for (int t = 0; t < NS; ++t) e[t] = buffer_load64(bs, (t * kWave + lane) * 8);
                 if (tid < kBracketBins<C> / 4) reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
                 split(n_ch, nwg);
                 float s1 = 0.0f, s2 = 0.0f;
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
     auto load_x = [&]() {
         const auto rs = buffer_of(x, xl ? (uint32_t)(nb * d) * 2 : 0u);
 #pragma unroll
-        for (int k = 0; k < XPT; ++k) xr[k] = buffer_load128(rs, tid * 16, k * kBlock * 16);
+        for (int k = 0; k < XPT; ++k) xr[k] = buffer_load128(rs, (k * kBlock + tid) * 16);
     };
     if constexpr (kEarlyX) load_x();
 
@@ -912,7 +912,7 @@ __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
                 // Past k_hi the weights are 0 and x may be anything finite of its rows.
                 const int xo = (r * d + min(kk, nsteps - 1) * 32 + 8 * g4) * 2;
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) xv[u][rt] = buffer_load128(xb, xo + rt * 16 * d * 2, 0);
+                for (int rt = 0; rt < RT; ++rt) xv[u][rt] = buffer_load128(xb, xo + rt * 16 * d * 2);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {

@@ -85,6 +85,57 @@ struct Int4Magic<kF16> {
     static constexpr float offset = 1032.0f;
 };
 
+// Codes of 8 columns of four kept rows (4 bytes a row: column 2k in the low nibble
+// of byte k) as B operands of four-row MFMAs, in the dtype of x, so that x enters
+// the product as it is, at any exponent.  A nibble n = q + 8 under an exponent is
+// exact: fp16 64 + n (n at bits 4..7, where the high one already is), bf16 16 + n
+// (the top four of its seven mantissa bits, both nibbles move).  The bias comes off
+// with the sum of x.  (Under fp16's 1024.0 the low nibble needs no move, nor under
+// bf16's 128.0, but fp32 sums then round at 1032 or 136 times that sum.)
+// bf16: the bytes of two rows and two columns go side by side, so that one shift
+// and one v_and_or serve four codes, and a second v_perm puts the exponent's byte
+// next to each: 36 instructions for the quad (40 with halves shifted one by one;
+// fp16 takes 32).
+template <int DT>
+struct Int4Quad {
+    static constexpr float bias = DT == kBF16 ? 16.0f + 8.0f : 64.0f + 8.0f;
+    static constexpr bool kB = DT == kBF16;
+    uint32_t mask_lo = kB ? 0x41414141u : 0x000F000Fu;   // bf16: the exponent's byte
+    uint32_t mask = kB ? 0x78787878u : 0x00F000F0u;
+    uint32_t M = kB ? 0x80808080u : 0x54005400u;
+    // Constants the compiler cannot see through, so that (p & mask) | M is one
+    // v_and_or_b32 rather than two instructions with literals.  (Not as inline
+    // asm: the compiler must see what an MFMA next to it reads and overwrites.)
+    __device__ __forceinline__ Int4Quad() {
+        if constexpr (kB) asm("" : "+v"(mask_lo), "+s"(mask), "+v"(M));
+        else asm("" : "+s"(mask_lo), "+s"(mask), "+v"(M));
+    }
+    // Columns 4h .. 4h + 3 (h = 0, 1).
+    __device__ __forceinline__ void columns(const uint32_t (&w)[4], int h, uint2 (&op)[4]) const {
+        if constexpr (kB) {
+            const uint32_t sel = 0x05010400u + (uint32_t)h * 0x02020202u;
+            const uint32_t p01 = __builtin_amdgcn_perm(w[1], w[0], sel);
+            const uint32_t p23 = __builtin_amdgcn_perm(w[3], w[2], sel);
+            const uint32_t l01 = ((p01 << 3) & mask) | M, l23 = ((p23 << 3) & mask) | M;
+            const uint32_t h01 = ((p01 >> 1) & mask) | M, h23 = ((p23 >> 1) & mask) | M;
+            auto half = [&](uint32_t v, uint32_t s) { return __builtin_amdgcn_perm(v, mask_lo, s); };
+            op[0] = make_uint2(half(l01, 0x00050004u), half(l23, 0x00050004u));
+            op[1] = make_uint2(half(h01, 0x00050004u), half(h23, 0x00050004u));
+            op[2] = make_uint2(half(l01, 0x00070006u), half(l23, 0x00070006u));
+            op[3] = make_uint2(half(h01, 0x00070006u), half(h23, 0x00070006u));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const uint32_t sel = (uint32_t)(2 * h + k) | ((uint32_t)(2 * h + k + 4) << 16);
+                const uint32_t p01 = __builtin_amdgcn_perm(w[1], w[0], sel);
+                const uint32_t p23 = __builtin_amdgcn_perm(w[3], w[2], sel);
+                op[2 * k] = make_uint2(((p01 & mask_lo) << 4) | M, ((p23 & mask_lo) << 4) | M);
+                op[2 * k + 1] = make_uint2((p01 & mask) | M, (p23 & mask) | M);
+            }
+        }
+    }
+};
+
 // (v & mask) | bits.  FUSED: one v_and_or_b32 (the compiler otherwise emits
 // two VOP2 instructions with literals); the asm form lengthens live ranges, so
 // it is used only where registers are not tight.
@@ -116,6 +167,18 @@ __device__ __forceinline__ v4f mfma16(uint2 a, uint2 b, v4f c) {
     else
         return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(v4h, a),
                                                      __builtin_bit_cast(v4h, b), c, 0, 0, 0);
+}
+
+// The same for 16 blocks of 4 x 4 x 4: block l / 4, A[l % 4][e] and B[e][l % 4],
+// D[e][l % 4].
+template <int DT>
+__device__ __forceinline__ v4f mfma4(uint2 a, uint2 b, v4f c) {
+    if constexpr (DT == kBF16)
+        return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(v4s, a),
+                                                      __builtin_bit_cast(v4s, b), c, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(v4h, a),
+                                                  __builtin_bit_cast(v4h, b), c, 0, 0, 0);
 }
 
 // 16- and 8-byte streaming loads (non-temporal hint: weights are read once
@@ -224,18 +287,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
               r2 = __builtin_amdgcn_readlane(v, 47);
     const int row = lane_id() >> 4;
     return v + (row >= 1 ? r0 : 0) + (row >= 2 ? r1 : 0) + (row >= 3 ? r2 : 0);
-}
-
-// Maximum over the wave (every lane active), in every lane.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor1, 0xF, 0xF, false));
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor2, 0xF, 0xF, false));
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppRor4, 0xF, 0xF, false));
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppRor8, 0xF, 0xF, false));
-    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = max(a[0], a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return max(b[0], b[1]);
 }
 
 // Sum over each quad of lanes (lanes 4j .. 4j+3), in every lane of the quad.

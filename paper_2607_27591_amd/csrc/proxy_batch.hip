@@ -1,23 +1,23 @@
 // Stage 1 of the sparse decode step for INT4 proxies and more than 16 batch rows
-// (more than four above d_model 4096): three launches that select once and read the
-// codes once for up to 64 rows.
+// (more than four above d_model 4096, more than one above 8192): three launches that
+// select once and read the codes once for up to 64 rows.
 //
 //  keys    max over the batch of |x_i|.
 //  gather  the input selection, once: every workgroup ranks the keys and lists the
 //          kept rows per quantisation group, padded to blocks of 16, and gathers its
 //          share of x (16 rows, a run of blocks) into the operand order of the next
-//          launch, in fp16 (bf16 x scaled by one power of two, exact down to 2^-28
-//          of the largest).
+//          launch.
 //  stream  one workgroup per column tile.  A wave takes a 64-byte window of the row
 //          segment (T = 64: both matrices; T = 128: one), one tile of 16 batch rows
-//          and a run of blocks.  A lane reads 4 bytes (8 columns) of four kept rows:
-//          the nibbles under the exponent of 64.0 are B operands of 16 x 16 x 16
-//          MFMAs, x (from L2, in operand order) the A operand, as in
-//          proxy_small_kernel but with 16 batch rows per tile.
+//          and a run of blocks.  A lane reads 4 bytes (8 columns) of four kept rows
+//          as B operands (Int4Quad) of 16 x 16 x 16 MFMAs, x (from L2, in operand
+//          order) the A operand, as in proxy_small_kernel but with 16 batch rows per
+//          tile.
 // The results meet in LDS in wave order.  At 4096 x 14336 and 64 rows keys, gather
 // and stream take 3, 8 and 33 us (the stream issues the dequantisation once per row
 // tile and window), against 4 x 27 us in launches of 16 rows, each listing again;
-// the call 108 us, from 178.
+// the call 108 us, from 178 (111 with bf16 operands, which take 36 instructions to
+// unpack a quad where fp16 takes 32).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"
@@ -36,7 +36,7 @@ struct BatchScratch {
         const size_t cap = (size_t)batch_list_cap(d, group);
         size_t o = 0;
         keys = o; o = align_up(o + (size_t)d * 4, 256);
-        head = o; o = align_up(o + 8, 256);                            // blocks, 2^-s
+        head = o; o = align_up(o + 4, 256);                            // blocks
         rows = o; o = align_up(o + cap * 2, 256);                      // row of every list position
         groups = o; o = align_up(o + (cap / kBatchBlock + 1) * 4, 256);   // group of every block (words: scalar loads)
         x = o; o = align_up(o + cap * 16 * (size_t)rt * 2, 256);       // [block][row tile][lane][4]
@@ -76,7 +76,6 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
     __shared__ TopKOrder<C> ord;
     __shared__ int gsel0[kMaxDModel / 128 + 1];   // kept rows before each group
     __shared__ int gstart[kMaxDModel / 128 + 1];  // padded list position of each group
-    __shared__ uint32_t wmax[kMaxBlockWaves];
     extern __shared__ __align__(16) unsigned char dsm[];
     uint16_t *rows_sh = reinterpret_cast<uint16_t *>(dsm);   // bit 15: a pad
     const BatchScratch L(d, group, rt_n);
@@ -96,11 +95,6 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
     } else {
         topk_select_u15<kBlock, C>(key, d, k_in, reinterpret_cast<uint32_t *>(dsm), ss, ord);
     }
-    uint32_t m = 0;
-#pragma unroll
-    for (int r = 0; r < C; ++r) m = max(m, key[r]);
-    m = wave_max_u32(m);
-    if (lane == 0) wmax[wid] = m;
     for (int g = tid; g <= ng; g += kBlock) gsel0[g] = topk_selected_before<kBlock, C>(ord, g * group);
     __syncthreads();
     if (wid == 0) {
@@ -133,15 +127,6 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
     }
     __syncthreads();
     const int n_pos = gstart[ng], nkb = n_pos / kBatchBlock;
-    float xscale = 1.0f, xunscale = 1.0f;
-    if constexpr (DT == kBF16) {
-        m = 0;
-#pragma unroll
-        for (int w = 0; w < kMaxBlockWaves; ++w) m = max(m, wmax[w]);
-        const int sx = min(100, max(-100, 141 - (int)(m >> 7)));   // 2^14 <= max |x| 2^s < 2^15
-        xscale = __uint_as_float((uint32_t)(127 + sx) << 23);
-        xunscale = __uint_as_float((uint32_t)(127 - sx) << 23);
-    }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
         uint16_t *rows = reinterpret_cast<uint16_t *>(scratch + L.rows);
         int *groups = reinterpret_cast<int *>(scratch + L.groups);
@@ -150,7 +135,6 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
             groups[kb] = (int)__umulhi((uint32_t)(rows_sh[kb * kBatchBlock] & 0x7FFFu), gmagic);
         if (tid == 0) {
             *reinterpret_cast<int *>(scratch + L.head) = nkb;
-            *reinterpret_cast<float *>(scratch + L.head + 4) = xunscale;
             if (sel_rule.tau_mode && sel_rule.count) *sel_rule.count = gsel0[ng];
         }
     }
@@ -167,16 +151,14 @@ __global__ __launch_bounds__(kBlock) void proxy_gather_kernel(
 #pragma unroll
         for (int q = 0; q < 4; ++q) h[q] = x[(size_t)min(b, B - 1) * d + (id[q] & 0x7FFFu)];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if constexpr (DT == kBF16) h[q] = float_to_f16_rne(bf16_lo(h[q]) * xscale);
+        for (int q = 0; q < 4; ++q)
             if ((id[q] & 0x8000u) || b >= B) h[q] = 0;
-        }
         xk[((size_t)kb * rt_n + rt) * kWave + lk] =
             make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
     }
 }
 
-template <int T, int RT>
+template <int DT, int T, int RT>
 __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
     const unsigned char *__restrict__ scratch, int nb, int d, int f, int group,
     const uint8_t *__restrict__ blob, float *__restrict__ scores, int act, ScoreBracket br) {
@@ -193,7 +175,6 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
     extern __shared__ __align__(16) unsigned char dsm[];
     uint32_t *offs = reinterpret_cast<uint32_t *>(dsm);   // row offsets of the list, then the sums
     const int nkb = *reinterpret_cast<const int *>(scratch + S.head);
-    const float xunscale = *reinterpret_cast<const float *>(scratch + S.head + 4);
     const uint16_t *rows = reinterpret_cast<const uint16_t *>(scratch + S.rows);
     const int *groups = reinterpret_cast<const int *>(scratch + S.groups);
     const uint32_t rstride = (uint32_t)L.row_stride;
@@ -213,9 +194,8 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
     v4f acc[CPL], tot[CPL], xacc = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int e = 0; e < CPL; ++e) acc[e] = tot[e] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    const uint2 ones = make_uint2(Int4Magic<kF16>::one, Int4Magic<kF16>::one);
-    uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u, M = 0x54005400u;   // (64.0, 64.0)
-    asm("" : "+s"(mask_lo), "+s"(mask_hi), "+v"(M));   // opaque: one v_and_or_b32 each
+    const uint2 ones = make_uint2(Int4Magic<DT>::one, Int4Magic<DT>::one);
+    const Int4Quad<DT> quad;
     if (kb0 < kb1) {
         uint32_t code[U][4];
         uint2 xq[U];
@@ -237,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
             for (int e = 0; e < CPL; ++e) {
                 const float s = f16_bits_to_float((e & 1) ? (sw[e >> 1] >> 16) : (sw[e >> 1] & 0xFFFFu));
 #pragma unroll
-                for (int j = 0; j < 4; ++j) tot[e][j] = fmaf(s, acc[e][j] - 72.0f * xacc[j], tot[e][j]);
+                for (int j = 0; j < 4; ++j) tot[e][j] = fmaf(s, acc[e][j] - Int4Quad<DT>::bias * xacc[j], tot[e][j]);
                 acc[e] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
             }
             xacc = v4f{0.0f, 0.0f, 0.0f, 0.0f};
@@ -253,16 +233,13 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
                     gcur = g;
                     sc = *reinterpret_cast<const uint4 *>(sbase + (size_t)gcur * 2 * T);
                 }
-                xacc = mfma16<kF16>(xq[u], ones, xacc);
+                xacc = mfma16<DT>(xq[u], ones, xacc);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t sel = (uint32_t)k | ((uint32_t)(k + 4) << 16);
-                    const uint32_t p01 = __builtin_amdgcn_perm(code[u][1], code[u][0], sel);
-                    const uint32_t p23 = __builtin_amdgcn_perm(code[u][3], code[u][2], sel);
-                    const uint2 lo = make_uint2(((p01 & mask_lo) << 4) | M, ((p23 & mask_lo) << 4) | M);
-                    const uint2 hi = make_uint2((p01 & mask_hi) | M, (p23 & mask_hi) | M);
-                    acc[2 * k] = mfma16<kF16>(xq[u], lo, acc[2 * k]);
-                    acc[2 * k + 1] = mfma16<kF16>(xq[u], hi, acc[2 * k + 1]);
+                for (int h = 0; h < 2; ++h) {
+                    uint2 op[4];
+                    quad.columns(code[u], h, op);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[4 * h + c] = mfma16<DT>(xq[u], op[c], acc[4 * h + c]);
                 }
                 load(u, min(kb + U, kb1 - 1));   // past the end: the last block again, unused
             }
@@ -274,7 +251,7 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
 #pragma unroll
     for (int e = 0; e < CPL; ++e)
         red[(wid * CPL + e) * kWave + lane] =
-            make_float4(tot[e][0] * xunscale, tot[e][1] * xunscale, tot[e][2] * xunscale, tot[e][3] * xunscale);
+            make_float4(tot[e][0], tot[e][1], tot[e][2], tot[e][3]);
     __syncthreads();
     // Every (row, column): the sums of the KS waves of gate and up in order, |act(g~)
     // u~|, the max over the row tiles, then over the 16 lanes that hold one column.
@@ -336,17 +313,17 @@ static hipError_t launch_gather_t(const void *x, int B, int d, int group, int k_
     return hipGetLastError();
 }
 
-template <int T, int RT>
+template <int DT, int T, int RT>
 static hipError_t launch_stream_t(const void *scratch, int nb, int d, int f, int group,
                                   const void *blob, float *scores, int act, ScoreBracket br,
                                   hipStream_t s) {
     const size_t list = (size_t)batch_list_cap(d, group) * 4, red = (size_t)kBlock * 32 * 4;
     const size_t lds = list > red ? list : red;   // 128 KiB
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(proxy_stream_kernel<T, RT>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(proxy_stream_kernel<DT, T, RT>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     const BlobLayout L(d, f, 4, group);
-    proxy_stream_kernel<T, RT><<<L.n_tiles, kBlock, lds, s>>>(
+    proxy_stream_kernel<DT, T, RT><<<L.n_tiles, kBlock, lds, s>>>(
         static_cast<const unsigned char *>(scratch), nb, d, f, group, static_cast<const uint8_t *>(blob),
         scores, act, br);
     return hipGetLastError();
@@ -368,7 +345,8 @@ hipError_t launch_proxy_batch(int dtype, const void *x, int batch, int d, int f,
     else e = dtype == kBF16 ? GA(kBF16, 16) : GA(kF16, 16);
 #undef GA
     if (e != hipSuccess) return e;
-#define ST(T_, RT_) return launch_stream_t<T_, RT_>(scratch, batch, d, f, group, blob, scores, act, br, s)
+#define ST(T_, RT_) return dtype == kBF16 ? launch_stream_t<kBF16, T_, RT_>(scratch, batch, d, f, group, blob, scores, act, br, s) \
+                                          : launch_stream_t<kF16, T_, RT_>(scratch, batch, d, f, group, blob, scores, act, br, s)
     if (proxy_tile(f) == 128) {
         if (rt == 1) ST(128, 1);
         if (rt == 2) ST(128, 2);

@@ -22,33 +22,29 @@
 // trips ahead is loaded as soon as one is used up, across rounds.
 //
 // Stream.  A lane reads 4 bytes (8 columns of one matrix) of four kept rows, a
-// quad.  Byte k of two rows side by side (v_perm) gives fp16 pairs: a nibble n =
-// q + 8 at bits 4..7 (the high one in place, the low one moved up) under the
-// exponent of 64.0 is exactly 64 + n.  Two such pairs are the B operand (4 rows of
-// k, the lane's column) of a 4 x 4 x 4 MFMA whose A operand is x of up to four
-// batch rows.  A ninth MFMA with B all ones sums x; at the end of a block 72 times
-// that sum comes off and the group's scale is applied.  (Under 1024.0 the low
-// nibble needs no move, but the fp32 sums then round at 1032 times the x sum:
-// scores 2e-5 off 64 bits, as the dot-product form is, against 2e-6.)  bf16 x are
-// scaled by a power of two per wave into fp16, exact down to 2^-28 of the wave's
-// largest.  Against v_dot2 per two weights and row, the vector unit issues 32
-// instead of 40 instructions per 32 weights, whatever the number of rows.
-// From the kernel's start to its last workgroup's scores, against that form: 4096 x
-// 12288, one row, 13.8 us (16.8); 8192 x 28672, one row, 27.8 (29.1); 4096 x 14336,
-// four rows, 17.4 (20.3 on the 16-row matrix-core kernel); 6272 x 13056, four rows,
-// the call 61.5 (70.0).  One batch of loads at a time, without the rolling
-// reload, took 15.5, 30.8 and 20.4.
+// quad, and makes them the B operands (4 rows of k, the lane's column; Int4Quad) of
+// 4 x 4 x 4 MFMAs whose A operand is x of up to four batch rows.  A ninth MFMA with
+// B all ones sums x; at the end of a block the bias times that sum comes off and the
+// group's scale is applied.  Batch rows meet nowhere before their scores, so their
+// ranges may differ at will.
+// From the kernel's start to its last workgroup's scores, against v_dot2 per two
+// weights and row: 4096 x 12288, one row, 13.8 us (16.8); 8192 x 28672, one row,
+// 27.8 (29.1); 4096 x 14336, four rows, 17.4 (20.3 on the 16-row matrix-core
+// kernel); 6272 x 13056, four rows, the call 61.5 (70.0).  One batch of loads at a
+// time, without the rolling reload, took 15.5, 30.8 and 20.4.  bf16 x scaled into
+// fp16, with fp16 codes, is no faster: the call takes 44.0 us either way at 4096 x
+// 12288 and 108.8 against 109.0 at 8192 x 28672, and a large row would take the
+// others' low bits.
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"
 
 namespace prox {
 
-constexpr float kSmallBias = 64.0f + 8.0f;   // of every column
 constexpr int kSmallHistWords = 4096 + 8;
 
 // LDS: the histogram | per wave, row offsets [lane group][trip][4] u32 (C * 64 in
-// all: rounds of up to 16 trips) and x [lane group][NB][trip][4] fp16; after the
+// all: rounds of up to 16 trips) and x [lane group][NB][trip][4]; after the
 // stream the cross-wave sums [16][NB][2T] take the space of the lists.
 __host__ __device__ constexpr size_t proxy_small_lds_bytes(int NB, int T, int C) {
     const size_t list = (size_t)C * kBlock * (4 + 2 * NB), red = (size_t)kMaxBlockWaves * NB * 2 * T * 4;
@@ -248,17 +244,6 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
     }
 
     // ---- the lists: early quads first, then the other kept inputs, padded ----
-    constexpr bool kScaleX = DT == kBF16;
-    float xscale = 1.0f, xunscale = 1.0f;   // 2^s and 2^-s: 2^14 <= largest |x| 2^s < 2^15
-    if constexpr (kScaleX) {
-        uint32_t m = 0;
-#pragma unroll
-        for (int r = 0; r < C; ++r) m = max(m, key[r]);
-        m = wave_max_u32(m);
-        const int sx = min(100, max(-100, 141 - (int)(m >> 7)));
-        xscale = __uint_as_float((uint32_t)(127 + sx) << 23);
-        xunscale = __uint_as_float((uint32_t)(127 - sx) << 23);
-    }
     int cnts = 0;    // lane r: listed inputs of block r
     uint64_t kept[C];
 #pragma unroll
@@ -313,11 +298,9 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
             // x: [lane group][NB][trip][4]
             const int xat = at + (at >> 2) / MAXT * ((NB - 1) * MAXT * 4);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                uint16_t xv = (uint16_t)(xw[b][r / 2] >> (16 * (r & 1)));
-                if constexpr (kScaleX) xv = float_to_f16_rne(bf16_lo(xv) * xscale);
-                xsh[xat + b * MAXT * 4] = is_kept && b < nb ? xv : (uint16_t)0;
-            }
+            for (int b = 0; b < NB; ++b)
+                xsh[xat + b * MAXT * 4] =
+                    is_kept && b < nb ? (uint16_t)(xw[b][r / 2] >> (16 * (r & 1))) : (uint16_t)0;
         }
         if (tile == 0 && in_mask && i < d) in_mask[i] = is_kept ? 1 : 0;
     }
@@ -351,12 +334,8 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int e = 0; e < CPL; ++e) tot[b][e] = 0.0f;
-    const uint2 ones = make_uint2(Int4Magic<kF16>::one, Int4Magic<kF16>::one);
-    // Constants the compiler cannot see through, so that (p & mask) | M is one
-    // v_and_or_b32 rather than two instructions with literals.  (Not as inline
-    // asm: the compiler must see what an MFMA next to it reads and overwrites.)
-    uint32_t mask_lo = 0x000F000Fu, mask_hi = 0x00F000F0u, M = 0x54005400u;   // (64.0, 64.0)
-    asm("" : "+s"(mask_lo), "+s"(mask_hi), "+v"(M));
+    const uint2 ones = make_uint2(Int4Magic<DT>::one, Int4Magic<DT>::one);
+    const Int4Quad<DT> quad;
     const uint2 *xlist = reinterpret_cast<const uint2 *>(xsh) + (lg * NB + (NB == 1 ? 0 : lane % NB)) * MAXT;
     v4f acc[CPL], xacc = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -371,7 +350,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
         for (int e = 0; e < CPL; ++e) {
             const float s = f16_bits_to_float((e & 1) ? (sw[e >> 1] >> 16) : (sw[e >> 1] & 0xFFFFu));
 #pragma unroll
-            for (int b = 0; b < NB; ++b) tot[b][e] = fmaf(s, acc[e][b] - kSmallBias * xacc[b], tot[b][e]);
+            for (int b = 0; b < NB; ++b) tot[b][e] = fmaf(s, acc[e][b] - Int4Quad<DT>::bias * xacc[b], tot[b][e]);
             acc[e] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
         }
         xacc = v4f{0.0f, 0.0f, 0.0f, 0.0f};
@@ -393,17 +372,13 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
             while (t >= end) flush();   // a round may be empty
             const uint2 xq = xlist[t];
             const uint4 o = olist[min(t + U, total - 1)];
-            const v4h a = __builtin_bit_cast(v4h, xq);
-            xacc = __builtin_amdgcn_mfma_f32_4x4x4f16(a, __builtin_bit_cast(v4h, ones), xacc, 0, 0, 0);
+            xacc = mfma4<DT>(xq, ones, xacc);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t sel = (uint32_t)k | ((uint32_t)(k + 4) << 16);
-                const uint32_t p01 = __builtin_amdgcn_perm(code[u][1], code[u][0], sel);
-                const uint32_t p23 = __builtin_amdgcn_perm(code[u][3], code[u][2], sel);
-                const uint2 lo = make_uint2(((p01 & mask_lo) << 4) | M, ((p23 & mask_lo) << 4) | M);
-                const uint2 hi = make_uint2((p01 & mask_hi) | M, (p23 & mask_hi) | M);
-                acc[2 * k] = __builtin_amdgcn_mfma_f32_4x4x4f16(a, __builtin_bit_cast(v4h, lo), acc[2 * k], 0, 0, 0);
-                acc[2 * k + 1] = __builtin_amdgcn_mfma_f32_4x4x4f16(a, __builtin_bit_cast(v4h, hi), acc[2 * k + 1], 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                uint2 op[4];
+                quad.columns(code[u], h, op);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[4 * h + c] = mfma4<DT>(xq, op[c], acc[4 * h + c]);
             }
             // The quad U trips on (past the end: the last one again, unused).
             load_quad(code[u], o);
@@ -416,7 +391,7 @@ __global__ __launch_bounds__(kBlock) void proxy_small_kernel(
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int e = 0; e < CPL; ++e) {
-            float t = tot[b][e] * xunscale;   // a power of two
+            float t = tot[b][e];
             if constexpr (LPS == 16) t = add_swap16(t);
             tot[b][e] = add_swap32(t);
         }

@@ -986,10 +986,13 @@ size_t stage2_down_lds_bytes(int dtype, int rt, int n_max, int groups) {
     return s > red ? s : red;
 }
 
-// The next bf16 part of v, and what remains.
+// The next bf16 part of v, and what remains.  Cut off, not rounded: a finite v never
+// becomes infinite, and three parts still hold the 24 bits.  Nothing remains of an
+// infinity (Inf - Inf would be NaN).
 __device__ __forceinline__ uint32_t bf16_part(float &v) {
-    const uint32_t h = float_to_bf16_rne(v);
-    v -= bf16_lo(h);
+    const uint32_t h = __float_as_uint(v) >> 16;
+    const float t = bf16_lo(h);
+    v = v == t ? 0.0f : v - t;
     return h;
 }
 

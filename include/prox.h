@@ -135,13 +135,16 @@ prox_status prox_unpack_proxy(const prox_proxy *p, int d_model, int d_ff, int8_t
                               uint16_t *scales_gate, int8_t *codes_up, uint16_t *scales_up,
                               hipStream_t stream);
 
-/* Workspace bytes needed by prox_ffn_sparse / prox_ffn_dense (16-bit
- * weights) for this shape and batch; 0 if unsupported.  The workspace needs
- * no initialisation.  It holds the proxy scores, the kept-channel list and
- * the partial y of Stage 2: one row set per Stage 2 workgroup (256), or, for
- * more than 8 batch rows at d_model >= 4096, per kept-channel group of the
- * matrix-core down projection (16 or fewer) plus s of the kept channels.  INT4 base
- * weights always take the 256 row sets: see prox_w4_workspace_bytes. */
+/* Workspace bytes of prox_ffn_sparse / prox_ffn_dense (16-bit weights) for
+ * this shape and every batch up to `batch`; 0 if unsupported.  One workspace
+ * of the largest batch's size serves all of them, and the size never falls as
+ * the batch grows.  It needs no initialisation.  It holds the proxy scores,
+ * the kept-channel list and the partial y of Stage 2: one row set per Stage 2
+ * workgroup (256), or, for more than 8 batch rows at d_model >= 4096, per
+ * kept-channel group of the matrix-core down projection (16 or fewer) plus s
+ * of the kept channels.  So a call of more than 8 rows takes less than one of
+ * 8 itself, and is accepted with what it takes.  INT4 base weights always take
+ * the 256 row sets: see prox_w4_workspace_bytes. */
 size_t prox_workspace_bytes(int d_model, int d_ff, int batch);
 
 /*
@@ -213,9 +216,12 @@ prox_status prox_ffn_sparse(const prox_weights *w, const prox_proxy *p, const vo
  * PROX_NOALLOC_SCRATCH_BYTES (32 MiB) per GPU, created with the library's code
  * object and held until the process ends.
  *   Arguments: as prox_ffn_sparse, without ws / ws_bytes.
- *   Limit: prox_workspace_bytes(d_model, d_ff, batch) must not exceed
- *   PROX_NOALLOC_SCRATCH_BYTES (e.g. 8192 x 28672 up to batch 2, d_model
- *   16384 at batch 1), else PROX_ERR_WORKSPACE before any HIP call.
+ *   Limit: what this batch itself takes must not exceed
+ *   PROX_NOALLOC_SCRATCH_BYTES, else PROX_ERR_WORKSPACE before any HIP call.
+ *   It does not where prox_workspace_bytes(d_model, d_ff, batch) does not
+ *   (e.g. 8192 x 28672 up to batch 2, d_model 16384 at batch 1); a call of
+ *   more than 8 rows at d_model >= 4096 takes less than that and may fit again
+ *   (8192 x 28672 with 9 to 64 rows).
  *   The first call on a device looks up that device's copy of the scratch
  *   (hipGetSymbolAddress); a failure there returns PROX_ERR_HIP.
  *   Every call on one GPU shares that GPU's scratch, which keeps the last
@@ -307,9 +313,9 @@ prox_status prox_pack_w4(const prox_weights *w, const prox_w4_weights *q, hipStr
 prox_status prox_unpack_w4(const prox_w4_weights *q, int matrix, int8_t *codes,
                            uint16_t *scales, hipStream_t stream);
 
-/* Workspace bytes needed by the calls on INT4 base weights (the *_w4 calls)
- * for this shape and batch (>= prox_workspace_bytes; equal up to 8 rows);
- * 0 if unsupported.  No initialisation needed. */
+/* Workspace bytes of the calls on INT4 base weights (the *_w4 calls) for this
+ * shape and every batch up to `batch` (>= prox_workspace_bytes; equal up to 8
+ * rows); 0 if unsupported.  No initialisation needed. */
 size_t prox_w4_workspace_bytes(int d_model, int d_ff, int batch);
 
 /* The dense FFN on the INT4 weights (every channel; the W4 baseline).

@@ -365,12 +365,12 @@ size_t prox_proxy_bytes(int d_model, int d_ff, prox_qfmt fmt, int group) {
 
 size_t prox_workspace_bytes(int d_model, int d_ff, int batch) {
     if (!shape_ok(d_model, d_ff) || batch < 1 || batch > PROX_MAX_BATCH) return 0;
-    return WsLayout(d_model, d_ff, batch, 16).total;
+    return ws_bytes_up_to(d_model, d_ff, batch, 16);
 }
 
 size_t prox_w4_workspace_bytes(int d_model, int d_ff, int batch) {
     if (!shape_ok(d_model, d_ff) || batch < 1 || batch > PROX_MAX_BATCH) return 0;
-    return WsLayout(d_model, d_ff, batch, 4).total;
+    return ws_bytes_up_to(d_model, d_ff, batch, 4);
 }
 
 prox_status prox_pack_proxy(const prox_weights *w, prox_proxy *p, hipStream_t stream) {

@@ -186,4 +186,14 @@ struct WsLayout {
     }
 };
 
+// Bytes of a workspace for every batch up to `batch`: each area at its largest.  (A
+// call's own batch may need far less: up to 8 rows write 256 sets of partial y,
+// more rows of 16-bit weights at most 16.)
+__host__ __device__ inline size_t ws_bytes_up_to(int d, int f, int batch, int wq) {
+    const WsLayout own(d, f, batch, wq);
+    const WsLayout vec(d, f, batch < kStage2MaxNB ? batch : kStage2MaxNB, wq);   // no sbuf
+    const size_t y_own = own.sbuf - own.ypart, y_vec = vec.sbuf - vec.ypart;
+    return own.total + (y_vec > y_own ? y_vec - y_own : 0);
+}
+
 }  // namespace prox

@@ -114,6 +114,19 @@ def test_sizes():
     assert prox.workspace_bytes(4096, 12288, 65, w4=True) == 0
 
 
+@pytest.mark.parametrize("w4", [False, True])
+@pytest.mark.parametrize("d,f", [(1024, 3072), (4096, 14336), (4096, 100), (4224, 65536),
+                                 (8192, 28672), (16384, 1), (16384, 65536)])
+def test_workspace_of_the_largest_batch_serves_the_smaller_ones(d, f, w4):
+    sizes = [prox.workspace_bytes(d, f, B, w4=w4) for B in range(1, 65)]
+    assert sizes == sorted(sizes)
+    # The 8-row kernel's partial y alone: 256 sets of 1, 2, 4 or 8 rows.
+    for B, n in enumerate(sizes, 1):
+        assert n >= 256 * (1 if B < 2 else 2 if B < 3 else 4 if B < 5 else 8) * d * 4
+    if not w4:   # INT4 base weights never take less
+        assert all(prox.workspace_bytes(d, f, B, w4=True) >= n for B, n in enumerate(sizes, 1))
+
+
 def test_stage1_kernel_selection():
     # The matrix-core Stage 1 takes INT4 proxies from three batch rows on up to
     # d_model 4096 and from five above, with 16 rows per launch while the

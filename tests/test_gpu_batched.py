@@ -33,3 +33,19 @@ def test_batched_parity(d, f, batch, dtype):
     y2 = prox.ffn_dense(case.w, prox.from_bits(np.ascontiguousarray(x[::-1]), dtype))
     torch.cuda.synchronize()
     assert np.array_equal(prox.to_bits(y2)[::-1], prox.to_bits(y))
+
+
+def test_one_workspace_serves_every_batch():
+    # A server allocates for its largest batch; the 8-row kernel's partial y then takes
+    # more than the matrix-core path's.  Each call as on a workspace of its own.
+    cfg = W.small_config(d=4096, f=700, batch=64, seed=41, in_frac=0.4, sigma_w=0.015)
+    case = make_case(cfg)
+    ws = prox.new_workspace(cfg.d_model, cfg.d_ff, 64)
+    for batch in (64, 8, 20, 5, 3, 16, 1):
+        print(f"[batched] one workspace, B={batch}", flush=True)
+        x = case.wl.x_vectors(1, batch)[0]
+        got, own = (run_sparse(case, x, cfg.k_in, cfg.k_ff, ws=w) for w in (ws, None))
+        assert np.array_equal(got.y, own.y) and np.array_equal(got.mask, own.mask)
+        xt = prox.from_bits(np.atleast_2d(x), cfg.dtype)
+        got, own = (prox.to_bits(prox.ffn_dense(case.w, xt, ws=w)) for w in (ws, None))
+        assert np.array_equal(got, own)

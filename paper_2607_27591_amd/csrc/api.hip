@@ -85,6 +85,7 @@ prox_status hip_status(hipError_t e) { return e == hipSuccess ? PROX_OK : PROX_E
 struct Ws {
     float *scores, *ypart, *sbuf;
     int32_t *klist;
+    size_t ypart_bytes;
 };
 
 Ws carve(void *ws, int d, int f, int batch, int wq) {
@@ -95,6 +96,7 @@ Ws carve(void *ws, int d, int f, int batch, int wq) {
     w.ypart = reinterpret_cast<float *>(b + L.ypart);
     w.klist = reinterpret_cast<int32_t *>(b + L.klist);
     w.sbuf = reinterpret_cast<float *>(b + L.sbuf);
+    w.ypart_bytes = L.sbuf - L.ypart;
     return w;
 }
 
@@ -246,7 +248,7 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
     if (route == kStage1Batch) {
         // Scratch: the partial-y area, which Stage 2 writes only afterwards.
         PROX_TRY(launch_proxy_batch(dt, x, batch, d, f, p->group, k_in, p->blob, in_mask, W.scores,
-                                    in_sel, m.act, br, W.ypart, stream));
+                                    in_sel, m.act, br, W.ypart, W.ypart_bytes, stream));
     } else {
         const int pnb = route == kStage1Mfma ? proxy_mfma_rows(d, p->group, k_in) : proxy_max_nb(d);
         for (int c0 = 0; c0 < batch; c0 += pnb) {

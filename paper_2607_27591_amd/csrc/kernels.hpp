@@ -49,11 +49,10 @@ hipError_t launch_proxy_small(int dtype, const void *x, int nb, int d, int f, in
                               ScoreBracket br, hipStream_t stream);
 
 // The same for every row of a batch in three launches that select once; scratch:
-// proxy_batch_scratch_bytes(d, group, batch) bytes, 256-byte aligned.
-size_t proxy_batch_scratch_bytes(int d, int group, int batch);
+// scratch_bytes >= BatchScratch(d, group, row tiles).total, 256-byte aligned.
 hipError_t launch_proxy_batch(int dtype, const void *x, int batch, int d, int f, int group, int k_in,
                               const void *blob, uint8_t *in_mask, float *scores, Select sel, int act,
-                              ScoreBracket br, void *scratch, hipStream_t stream);
+                              ScoreBracket br, void *scratch, size_t scratch_bytes, hipStream_t stream);
 
 // Stage 1 on the matrix cores for INT4 proxies and d <= 4096: batch rows [row0, row0 + nb)
 // with nb <= proxy_mfma_rows(d, group, k_in) (16, 8, or 0 when the kept-row

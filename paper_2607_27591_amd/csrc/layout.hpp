@@ -130,6 +130,28 @@ __host__ __device__ inline int ypart_rows(int batch) {
                                  : (batch + kStage2MaxNB - 1) / kStage2MaxNB * kStage2MaxNB;
 }
 
+// Scratch of the batch Stage 1 (proxy_batch.hip) for rt tiles of 16 rows, over the
+// partial-y area, which Stage 2 fills later: it fits there for every shape, group and
+// batch (swept by a test, checked by the host for each call).
+constexpr int kBatchBlock = 16;   // kept rows per block
+
+__host__ __device__ inline int batch_list_cap(int d, int group) {   // every input kept
+    return d + d / group * (kBatchBlock - 1);
+}
+struct BatchScratch {
+    size_t keys, head, rows, groups, x, total;
+    __host__ __device__ BatchScratch(int d, int group, int rt) {
+        const size_t cap = (size_t)batch_list_cap(d, group);
+        size_t o = 0;
+        keys = o; o = align_up(o + (size_t)d * 4, 256);
+        head = o; o = align_up(o + 4, 256);                            // blocks
+        rows = o; o = align_up(o + cap * 2, 256);                      // row of every list position
+        groups = o; o = align_up(o + (cap / kBatchBlock + 1) * 4, 256);   // group of every block (words: scalar loads)
+        x = o; o = align_up(o + cap * 16 * (size_t)rt * 2, 256);       // [block][row tile][lane][4]
+        total = o;
+    }
+};
+
 // How a launch selects its set (Sec. 4.1 masks): by count (the top-k reading,
 // App. A.6) or, with tau_mode, by the layer-wise threshold rule |z| >= tau,
 // whose realised count then goes to *count (when count is not NULL).

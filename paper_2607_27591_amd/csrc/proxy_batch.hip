@@ -24,26 +24,6 @@
 
 namespace prox {
 
-constexpr int kBatchBlock = 16;   // kept rows per block
-
-__host__ __device__ inline int batch_list_cap(int d, int group) {   // every input kept
-    return d + d / group * (kBatchBlock - 1);
-}
-// Scratch of the three launches, in the partial-y area, which Stage 2 fills later.
-struct BatchScratch {
-    size_t keys, head, rows, groups, x, total;
-    __host__ __device__ BatchScratch(int d, int group, int rt) {
-        const size_t cap = (size_t)batch_list_cap(d, group);
-        size_t o = 0;
-        keys = o; o = align_up(o + (size_t)d * 4, 256);
-        head = o; o = align_up(o + 4, 256);                            // blocks
-        rows = o; o = align_up(o + cap * 2, 256);                      // row of every list position
-        groups = o; o = align_up(o + (cap / kBatchBlock + 1) * 4, 256);   // group of every block (words: scalar loads)
-        x = o; o = align_up(o + cap * 16 * (size_t)rt * 2, 256);       // [block][row tile][lane][4]
-        total = o;
-    }
-};
-
 // 128 inputs per workgroup, four groups of threads over the batch rows.
 __global__ __launch_bounds__(256) void proxy_keys_kernel(const uint16_t *__restrict__ x, int B, int d,
                                                          uint32_t *__restrict__ keys) {
@@ -294,10 +274,6 @@ __global__ __launch_bounds__(kBlock) void proxy_stream_kernel(
     }
 }
 
-size_t proxy_batch_scratch_bytes(int d, int group, int batch) {
-    return BatchScratch(d, group, stage2_row_tiles(batch)).total;
-}
-
 template <int DT, int C>
 static hipError_t launch_gather_t(const void *x, int B, int d, int group, int k_in, int rt,
                                   uint8_t *in_mask, Select sel, void *scratch, hipStream_t s) {
@@ -331,10 +307,11 @@ static hipError_t launch_stream_t(const void *scratch, int nb, int d, int f, int
 
 hipError_t launch_proxy_batch(int dtype, const void *x, int batch, int d, int f, int group, int k_in,
                               const void *blob, uint8_t *in_mask, float *scores, Select sel, int act,
-                              ScoreBracket br, void *scratch, hipStream_t s) {
+                              ScoreBracket br, void *scratch, size_t scratch_bytes, hipStream_t s) {
     if (batch < 1 || batch > 64 || d % 128 != 0) return hipErrorInvalidValue;
     const int rt = stage2_row_tiles(batch);
     const BatchScratch L(d, group, rt);
+    if (L.total > scratch_bytes) return hipErrorInvalidValue;
     proxy_keys_kernel<<<d / 128, 256, 0, s>>>(static_cast<const uint16_t *>(x), batch, d,
                                               reinterpret_cast<uint32_t *>(static_cast<char *>(scratch) + L.keys));
     hipError_t e = hipGetLastError();

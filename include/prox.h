@@ -148,16 +148,16 @@ prox_status prox_unpack_proxy(const prox_proxy *p, int d_model, int d_ff, int8_t
 size_t prox_workspace_bytes(int d_model, int d_ff, int batch);
 
 /*
- * Batch rows one launch of the 16-row matrix-core Stage-1 kernel can cover for
- * this shape (for inspection and tests), or 0 (an INT8 or unquantised proxy,
- * fewer than three batch rows up to d_model 4096 or fewer than five above, a
- * kept-input list too long for the LDS, or an unsupported shape).  Calls with
- * an INT4 proxy take that kernel for 5 to 16 rows up to d_model 4096, the
- * small-batch kernel for fewer rows (one above d_model 8192), and else the
- * batch kernels, which select once for every row.  k_in is the kept-input
- * count; the threshold entry point sizes its list for k_in = d_model.  Host
- * only, no HIP calls.  The kernels compute the same proxy in a different fp32
- * summation order.
+ * Batch rows per launch of the 16-row matrix-core Stage-1 kernel when a call
+ * takes it (for inspection and tests), else 0.  Calls with an INT4 proxy take
+ * that kernel for 5 to 16 rows up to d_model 4096 (16 rows a launch, or 8
+ * where the kept-input list would not fit the LDS beside 16 rows of x), the
+ * small-batch kernel up to four rows (one above d_model 8192), and else the
+ * batch kernels, which select once for every row; INT8 and unquantised proxies
+ * take the dot-product kernel.  k_in is the kept-input count; the threshold
+ * entry point sizes its list for k_in = d_model.  0 too for an unsupported
+ * shape.  Host only, no HIP calls.  The kernels compute the same proxy in a
+ * different fp32 summation order.
  */
 int prox_stage1_mfma_rows(int d_model, prox_qfmt fmt, int group, int batch, int k_in);
 

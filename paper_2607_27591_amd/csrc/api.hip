@@ -155,11 +155,6 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
     return PROX_OK;
 }
 
-// Batch rows per matrix-core Stage-1 launch, or 0 for the dot-product kernel.
-int stage1_mfma_rows(int d, int qbits, int group, int batch, int k_in) {
-    return qbits == 4 && batch >= proxy_mfma_min_rows(d) ? proxy_mfma_rows(d, group, k_in) : 0;
-}
-
 // Stage 1 kernels of a call.  INT4 proxies: up to four rows (one above d = 8192) on
 // the small-batch kernel (4096 x 14336, four rows: the call takes 54 us, 57 on the
 // 16-row matrix-core kernel); up to 16 rows at d <= 4096 on that kernel (16 rows:
@@ -173,6 +168,11 @@ Stage1Route stage1_route(int d, int qbits, int batch) {
     if (qbits != 4) return kStage1Dot;
     if (batch <= proxy_max_nb(d)) return kStage1Small;
     return d <= 4096 && batch <= 16 ? kStage1Mfma : kStage1Batch;
+}
+
+// Batch rows per launch of the 16-row kernel, or 0 when the call takes another.
+int stage1_mfma_rows(int d, int qbits, int group, int batch, int k_in) {
+    return stage1_route(d, qbits, batch) == kStage1Mfma ? proxy_mfma_rows(d, group, k_in) : 0;
 }
 
 // The bracket of a top-k call's channel selection (ScoreBracket).  Its order
@@ -250,7 +250,8 @@ prox_status sparse_run(const Model &m, const prox_proxy *p, const void *x, int b
         PROX_TRY(launch_proxy_batch(dt, x, batch, d, f, p->group, k_in, p->blob, in_mask, W.scores,
                                     in_sel, m.act, br, W.ypart, W.ypart_bytes, stream));
     } else {
-        const int pnb = route == kStage1Mfma ? proxy_mfma_rows(d, p->group, k_in) : proxy_max_nb(d);
+        const int pnb = route == kStage1Mfma ? stage1_mfma_rows(d, qbits, p->group, batch, k_in)
+                                             : proxy_max_nb(d);
         for (int c0 = 0; c0 < batch; c0 += pnb) {
             const int nb = batch - c0 < pnb ? batch - c0 : pnb;
             const ScoreBracket out = c0 + pnb >= batch ? br : ScoreBracket{};

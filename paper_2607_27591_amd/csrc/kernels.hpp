@@ -66,9 +66,6 @@ hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, 
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                              int32_t *klist, int list_mode, hipStream_t stream);
-// Batch rows from which prox_stage1_mfma_rows reports that kernel: 3 up to d_model
-// 4096, 5 above.  (Which kernel a call takes: stage1_route.)
-inline int proxy_mfma_min_rows(int d) { return d <= 4096 ? 3 : 5; }
 
 // The three matrices of Stage 2: channel-major 16-bit rows (wq == 16), or
 // INT4 codes with fp16 scales per (channel, group along d), laid out as

@@ -195,8 +195,8 @@ def proxy_bytes(d_model: int, d_ff: int, fmt: int, group: int) -> int:
 
 
 def stage1_mfma_rows(d_model: int, fmt: int, group: int, batch: int, k_in: int) -> int:
-    """Batch rows per matrix-core Stage-1 launch, 0 when the dot-product
-    kernel runs (threshold mode: pass k_in = d_model)."""
+    """Batch rows per launch of the 16-row matrix-core Stage-1 kernel, 0 when a
+    call takes another one (threshold mode: pass k_in = d_model)."""
     return int(lib().prox_stage1_mfma_rows(d_model, fmt, group, batch, k_in))
 
 

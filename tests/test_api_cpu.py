@@ -128,26 +128,27 @@ def test_workspace_of_the_largest_batch_serves_the_smaller_ones(d, f, w4):
 
 
 def test_stage1_kernel_selection():
-    # The matrix-core Stage 1 takes INT4 proxies from three batch rows on up to
-    # d_model 4096 and from five above, with 16 rows per launch while the
-    # kept-row list and 16 x rows fit the LDS, then 8; otherwise (and for
-    # INT8, unquantised or bad shapes) the dot-product kernel (0).
+    # The 16-row matrix-core Stage 1 takes INT4 proxies for 5 to 16 batch rows up to
+    # d_model 4096, 16 rows per launch while the kept-row list and 16 x rows fit the
+    # LDS, else 8; every other call (0) takes the small-batch, the batch or, for INT8
+    # and unquantised proxies, the dot-product kernel.
     rows = prox.stage1_mfma_rows
-    assert rows(4096, prox.INT4, 128, 16, 2048) == 16
-    assert rows(4096, prox.INT4, 128, 5, 2048) == 16
-    assert rows(4096, prox.INT4, 128, 3, 2048) == 16
-    assert rows(4096, prox.INT4, 128, 2, 2048) == 0        # two rows: dot product
-    assert rows(8192, prox.INT4, 128, 4, 3277) == 0        # four rows at 8192: dot product
-    assert rows(8192, prox.INT4, 128, 5, 3277) == 8
-    assert rows(4096, prox.INT4, 128, 12, 4096) == 8       # threshold-mode list
-    assert rows(8192, prox.INT4, 128, 16, 3277) == 8
-    assert rows(8192, prox.INT4, 128, 16, 8192) == 0       # list too long
-    assert rows(16384, prox.INT4, 128, 6, 4915) == 8
+    for d in (128, 1024, 4096):
+        for B in (1, 4, 5, 16, 17, 64):
+            assert rows(d, prox.INT4, 128, B, d // 2) == (16 if 5 <= B <= 16 else 0), (d, B)
+            # Threshold mode and a full keep: the list of every input.
+            want = (8 if d == 4096 else 16) if 5 <= B <= 16 else 0
+            assert rows(d, prox.INT4, 128, B, d) == want, (d, B)
+    for d in (4224, 8192, 8320, 16384):
+        for B in (1, 2, 4, 5, 16, 17, 64):
+            assert rows(d, prox.INT4, 128, B, d // 3) == 0, (d, B)
+            assert rows(d, prox.INT4, 128, B, d) == 0, (d, B)
+    assert rows(4096, prox.INT4, 4096, 8, 3968) == 16      # per-row groups: few pads
     assert rows(4096, prox.INT8, 128, 16, 2048) == 0
     assert rows(4096, prox.NONE, 4096, 16, 2048) == 0
     assert rows(4096, prox.INT4, 96, 16, 2048) == 0        # group % 128
     assert rows(4096, prox.INT4, 128, 65, 2048) == 0       # batch
-    assert rows(4096, prox.INT4, 128, 64, 2048) == 16
+    assert rows(4096, prox.INT4, 128, 0, 2048) == 0
     assert rows(4096, prox.INT4, 128, 16, 0) == 0          # k_in
     assert rows(4096, prox.INT4, 128, 16, 4097) == 0
 

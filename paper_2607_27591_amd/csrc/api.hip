@@ -130,8 +130,7 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
     if (rows == kStage2MfmaRows) {
         const int n_max = scores && !sel.tau_mode ? k_ff : f;
         PROX_TRY(launch_stage2_mfma(dt, xb, batch, d, f, m.s2, scores, k_ff, mask, scores_copy,
-                                    W.sbuf, nwg, sel, br, m.act, W.klist,
-                                    scores ? kListWrite : kListNone, stream));
+                                    W.sbuf, nwg, sel, br, m.act, W.klist, stream));
         PROX_TRY(launch_stage2_down(dt, batch, d, f, m.s2.wd, W.sbuf, scores ? W.klist : nullptr,
                                     n_max, W.ypart, ystride, stream));
         if (events) PROX_TRY(hipEventRecord(events[2], stream));

@@ -136,18 +136,12 @@ struct Int4Quad {
     }
 };
 
-// (v & mask) | bits.  FUSED: one v_and_or_b32 (the compiler otherwise emits
-// two VOP2 instructions with literals); the asm form lengthens live ranges, so
-// it is used only where registers are not tight.
-template <bool FUSED>
+// (v & mask) | bits as one v_and_or_b32 (the compiler otherwise emits two VOP2
+// instructions with literals).
 __device__ __forceinline__ uint32_t and_or(uint32_t v, uint32_t mask, uint32_t bits) {
-    if constexpr (FUSED) {
-        uint32_t r;
-        asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(bits));
-        return r;
-    } else {
-        return (v & mask) | bits;
-    }
+    uint32_t r;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(mask), "v"(bits));
+    return r;
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -293,28 +287,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 __device__ __forceinline__ uint32_t quad_sum_u32(uint32_t v) {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor1, 0xF, 0xF, false);
     return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor2, 0xF, 0xF, false);
-}
-
-// Block-wide exclusive prefix sum of one int per thread (NT threads); also
-// returns the block total.  `sh` is LDS scratch of NT/64 + 1 ints.
-template <int NT>
-__device__ __forceinline__ int block_exclusive_scan(int v, int *sh, int &total) {
-    constexpr int NW = NT / kWave;
-    const int lane = lane_id(), wid = threadIdx.x / kWave;
-    int incl = wave_inclusive_scan(v);
-    if (lane == kWave - 1) sh[wid] = incl;
-    __syncthreads();
-    if (wid == 0) {
-        int wv = lane < NW ? sh[lane] : 0;
-        int wi = wave_inclusive_scan(wv);
-        if (lane < NW) sh[lane] = wi - wv;
-        if (lane == NW - 1) sh[NW] = wi;
-    }
-    __syncthreads();
-    int res = sh[wid] + incl - v;
-    total = sh[NW];
-    __syncthreads();
-    return res;
 }
 
 }  // namespace prox

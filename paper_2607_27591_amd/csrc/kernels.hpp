@@ -94,8 +94,8 @@ hipError_t launch_stage2(int dtype, const void *x, int nb, int d, int f, const S
                          int32_t *klist, int klist_mode, hipStream_t stream);
 // Stage 2 for up to kStage2MfmaMaxRows batch rows (16-bit weights, d >= 4096:
 // stage2_mfma_ok) in two launches.  launch_stage2_mfma selects like
-// launch_stage2 (same kept-list modes; the sparse path must write or read
-// klist, since the down launch takes the kept channels from it), runs gate/up
+// launch_stage2 (the sparse path writes klist, as the down launch takes the kept
+// channels from it), runs gate/up
 // on the matrix cores and writes s of kept-list position p and batch row b to
 // sbuf[p * R + b], R = 16 stage2_row_tiles(nb).  launch_stage2_down then splits
 // the kept list (klist, or every channel when klist is NULL) into
@@ -105,7 +105,7 @@ bool stage2_mfma_ok(int d, int wq);
 hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               const Stage2Weights &w, const float *scores, int k_ff,
                               uint8_t *mask, float *scores_copy, float *sbuf, int nwg, Select sel,
-                              ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t stream);
+                              ScoreBracket br, int act, int32_t *klist, hipStream_t stream);
 hipError_t launch_stage2_down(int dtype, int nb, int d, int f, const void *wd, const float *sbuf,
                               const int32_t *klist, int n_max, float *ypart, int ystride,
                               hipStream_t stream);

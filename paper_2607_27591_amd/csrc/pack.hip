@@ -33,10 +33,6 @@ __device__ uint16_t f64_to_f16_rne(double v) {
     return sign | (uint16_t)keep;   // 1024 encodes the smallest normal
 }
 
-__device__ __forceinline__ double f16_to_f64(uint16_t h) {
-    return (double)f16_bits_to_float(h);
-}
-
 template <int DT>
 __device__ __forceinline__ double w_to_f64(uint16_t h) { return (double)half_to_float<DT>(h); }
 

@@ -53,7 +53,7 @@ __host__ __device__ inline size_t mfma_lds_bytes(int k_in, int ng, int nx) {
     return m > kSelHistU16Bytes ? m : kSelHistU16Bytes;
 }
 
-template <int DT, int T, int C, int NX>
+template <int DT, int T, int NX>
 __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
     const uint16_t *__restrict__ x_all, int B_all, int row0, int nb, int d, int f, int group,
     int k_in, const uint8_t *__restrict__ blob, uint8_t *__restrict__ in_mask,
@@ -61,6 +61,7 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
     int32_t *__restrict__ klist, int list_mode) {   // kept-row list of a multi-launch call
     static_assert(T == 64 || T == 128, "tile widths of the blob layout");
     static_assert(NX == 8 || NX == 16, "x rows kept in LDS");
+    constexpr int C = 4;                             // inputs per thread: d <= 4096
     constexpr int WH = T / 64;                       // 64-column halves per tile
     constexpr int WPG = kMaxBlockWaves / (WH * 2);   // waves per (half, matrix)
     constexpr uint32_t M = Int4Magic<DT>::pair;
@@ -126,44 +127,35 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
         }
     } else {
         // ---- input selection: key = max_b |x_{b,i}| bits ----
-        // x is read XQ rows at a time, two rows' 16-bit values per register,
-        // so a round's loads are in flight together (XQ * C = 64 values in 32
-        // registers per thread: one round trip for 16 rows of d <= 4096; two
-        // rows at a time for d > 8192, where registers are short).
-        constexpr int XQ = C <= 8 ? 64 / C : 2;
-        uint32_t key[C];
-    #pragma unroll
-        for (int r = 0; r < C; ++r) key[r] = 0u;
-        // With 4 inputs per thread one round holds all 16 rows: a single
-        // launch keeps them in registers for the list instead of reloading.
-        constexpr bool kKeepX = C == 4;
-        uint32_t raw[XQ / 2][C];
-        for (int b0 = 0; b0 < B_all; b0 += XQ) {
-    #pragma unroll
-            for (int q = 0; q < XQ / 2; ++q) {
-                const uint16_t *xa = x_all + (size_t)min(b0 + 2 * q, B_all - 1) * d;
-                const uint16_t *xc = x_all + (size_t)min(b0 + 2 * q + 1, B_all - 1) * d;
-    #pragma unroll
-                for (int r = 0; r < C; ++r)
-                    raw[q][r] = (uint32_t)xa[min(r * kBlock + tid, d - 1)] |
-                                ((uint32_t)xc[min(r * kBlock + tid, d - 1)] << 16);
-            }
-    #pragma unroll
-            for (int q = 0; q < XQ / 2; ++q)
-    #pragma unroll
-                for (int r = 0; r < C; ++r)
-                    if (r * kBlock + tid < d)
-                        key[r] = max(key[r], max(raw[q][r] & 0x7FFFu, (raw[q][r] >> 16) & 0x7FFFu));
+        // The x of all rows (at most 16), two rows' 16-bit values per register:
+        // all loads in flight together, and the list's values stay at hand.
+        uint32_t key[C], raw[8][C];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint16_t *xa = x_all + (size_t)min(2 * q, B_all - 1) * d;
+            const uint16_t *xc = x_all + (size_t)min(2 * q + 1, B_all - 1) * d;
+#pragma unroll
+            for (int r = 0; r < C; ++r)
+                raw[q][r] = (uint32_t)xa[min(r * kBlock + tid, d - 1)] |
+                            ((uint32_t)xc[min(r * kBlock + tid, d - 1)] << 16);
+        }
+#pragma unroll
+        for (int r = 0; r < C; ++r) {
+            key[r] = 0u;
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (r * kBlock + tid < d)
+                    key[r] = max(key[r], max(raw[q][r] & 0x7FFFu, (raw[q][r] >> 16) & 0x7FFFu));
         }
         uint64_t sel = 0;
         if (sel_rule.tau_mode) {
-    #pragma unroll
+#pragma unroll
             for (int r = 0; r < C; ++r) {
                 const bool in = r * kBlock + tid < d && half_to_float<DT>((uint16_t)key[r]) >= sel_rule.tau;
                 sel |= (uint64_t)in << r;
             }
             topk_order<kBlock, C>(sel, ord);
-            if (tile == 0 && row0 == 0 && tid == 0 && sel_rule.count)
+            if (tile == 0 && tid == 0 && sel_rule.count)
                 *sel_rule.count = topk_selected_before<kBlock, C>(ord, C * kBlock);
         } else {
             topk_select_u15<kBlock, C>(key, d, k_in, reinterpret_cast<uint32_t *>(dsm), ss, ord);
@@ -178,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
         // The 64 inputs of a (row, wave) share one quantisation group: a kept
         // input's position is wave-uniform table entries plus a lane count.
         const int swid = wave_id();
-    #pragma unroll
+#pragma unroll
         for (int r = 0; r < C; ++r) {
             const int i = r * kBlock + tid;
             const uint64_t bs = ord.sel[r][swid];
@@ -189,49 +181,17 @@ __global__ __launch_bounds__(kBlock) void proxy_mfma_kernel(
                        : -1;
             if (s) rows_sh[pos[r]] = (uint16_t)i;
         }
-        // Only the nb real batch rows are stored: the stream feeds zeros for the
-        // others.  XL rows at a time, only the kept inputs loaded, all of a
-        // round in flight together.
-        constexpr int XL = 32 / C;   // rows per round: 32 values per thread
-        if (kKeepX && B_all <= XQ && row0 == 0 && nb == B_all) {
-            // raw[q][r] already holds rows 2q and 2q + 1 side by side: NX rows
-            // of a kept input are NX / 8 16-byte stores (rows past nb hold
-            // copies, never read).
-    #pragma unroll
-            for (int r = 0; r < C; ++r)
-                if (pos[r] >= 0) {
-                    uint4 *dst = reinterpret_cast<uint4 *>(xs_sh + (size_t)pos[r] * NX);
-    #pragma unroll
-                    for (int h = 0; h < NX / 8; ++h)
-                        dst[h] = make_uint4(raw[4 * h][r], raw[4 * h + 1][r], raw[4 * h + 2][r], raw[4 * h + 3][r]);
-                }
-        } else
-        for (int b0 = 0; b0 < nb; b0 += XL) {
-            uint16_t xv[XL][C];
-    #pragma unroll
-            for (int q = 0; q < XL; ++q) {
-                const uint16_t *xb = x_all + (size_t)(row0 + min(b0 + q, nb - 1)) * d;
-    #pragma unroll
-                for (int r = 0; r < C; ++r) xv[q][r] = pos[r] >= 0 ? xb[min(r * kBlock + tid, d - 1)] : (uint16_t)0;
+        // raw[q][r] holds rows 2q and 2q + 1 side by side: the NX rows of a kept input
+        // are NX / 8 16-byte stores (rows past nb hold copies, never read: the stream
+        // feeds zeros for them).
+#pragma unroll
+        for (int r = 0; r < C; ++r)
+            if (pos[r] >= 0) {
+                uint4 *dst = reinterpret_cast<uint4 *>(xs_sh + (size_t)pos[r] * NX);
+#pragma unroll
+                for (int h = 0; h < NX / 8; ++h)
+                    dst[h] = make_uint4(raw[4 * h][r], raw[4 * h + 1][r], raw[4 * h + 2][r], raw[4 * h + 3][r]);
             }
-            // The round's XL rows of a kept input are contiguous: one store
-            // (rows past nb hold copies, never read; b0 + XL <= NX).
-    #pragma unroll
-            for (int r = 0; r < C; ++r)
-                if (pos[r] >= 0) {
-                    uint32_t w[XL / 2];
-    #pragma unroll
-                    for (int q = 0; q < XL / 2; ++q)
-                        w[q] = (uint32_t)xv[2 * q][r] | ((uint32_t)xv[2 * q + 1][r] << 16);
-                    uint16_t *dst = xs_sh + (size_t)pos[r] * NX + b0;
-                    if constexpr (XL == 8)
-                        *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
-                    else if constexpr (XL == 4)
-                        *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
-                    else
-                        *reinterpret_cast<uint32_t *>(dst) = w[0];
-                }
-        }
         if (list_mode == kListWrite && tile == 0) {   // the list for the later launches
 #pragma unroll
             for (int r = 0; r < C; ++r)
@@ -408,7 +368,7 @@ int proxy_mfma_rows(int d, int group, int k_in) {
     return 0;
 }
 
-template <int DT, int T, int C, int NX>
+template <int DT, int T, int NX>
 static hipError_t launch_mfma_t(const void *x_all, int B_all, int row0, int nb, int d, int f,
                                 int group, int k_in, const void *blob, uint8_t *in_mask,
                                 float *scores, int accumulate, Select sel, int act, ScoreBracket br,
@@ -416,23 +376,23 @@ static hipError_t launch_mfma_t(const void *x_all, int B_all, int row0, int nb, 
     const BlobLayout L(d, f, 4, group);
     const size_t lds = mfma_lds_bytes(k_in, d / group, NX);
     const hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void *>(proxy_mfma_kernel<DT, T, C, NX>),
+        reinterpret_cast<const void *>(proxy_mfma_kernel<DT, T, NX>),
         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    proxy_mfma_kernel<DT, T, C, NX><<<L.n_tiles, kBlock, lds, s>>>(
+    proxy_mfma_kernel<DT, T, NX><<<L.n_tiles, kBlock, lds, s>>>(
         static_cast<const uint16_t *>(x_all), B_all, row0, nb, d, f, group, k_in,
         static_cast<const uint8_t *>(blob), in_mask, scores, accumulate, sel, act, br, klist, list_mode);
     return hipGetLastError();
 }
 
 template <int DT, int T>
-static hipError_t launch_mfma_c(const void *x_all, int B_all, int row0, int nb, int d, int f,
+static hipError_t launch_mfma_nx(const void *x_all, int B_all, int row0, int nb, int d, int f,
                                 int group, int k_in, const void *blob, uint8_t *in_mask,
                                 float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                                 int32_t *klist, int list_mode, hipStream_t s) {
     const int nx = proxy_mfma_rows(d, group, k_in);
-#define MF(C_, NX_) launch_mfma_t<DT, T, C_, NX_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
-    return nx == 16 ? MF(4, 16) : MF(4, 8);
+#define MF(NX_) launch_mfma_t<DT, T, NX_>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
+    return nx == 16 ? MF(16) : MF(8);
 #undef MF
 }
 
@@ -440,14 +400,16 @@ hipError_t launch_proxy_mfma(int dtype, const void *x_all, int B_all, int row0, 
                              int f, int group, int k_in, const void *blob, uint8_t *in_mask,
                              float *scores, int accumulate, Select sel, int act, ScoreBracket br,
                              int32_t *klist, int list_mode, hipStream_t s) {
-    // Wider d takes the batch kernels: 4 input rows per thread here.
-    if (nb < 1 || d > 4 * kBlock || nb > proxy_mfma_rows(d, group, k_in)) return hipErrorInvalidValue;
+    // Wider d and more rows take the batch kernels.
+    if (nb < 1 || d > 4 * kBlock || B_all > 16 || nb > proxy_mfma_rows(d, group, k_in))
+        return hipErrorInvalidValue;
     if (list_mode != kListNone && !klist) return hipErrorInvalidValue;
+    if ((row0 > 0) != (list_mode == kListRead)) return hipErrorInvalidValue;   // the first launch selects
     if (proxy_tile(f) == 128)
-        return dtype == kBF16 ? launch_mfma_c<kBF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
-                              : launch_mfma_c<kF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
-    return dtype == kBF16 ? launch_mfma_c<kBF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
-                          : launch_mfma_c<kF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
+        return dtype == kBF16 ? launch_mfma_nx<kBF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
+                              : launch_mfma_nx<kF16, 128>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
+    return dtype == kBF16 ? launch_mfma_nx<kBF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s)
+                          : launch_mfma_nx<kF16, 64>(x_all, B_all, row0, nb, d, f, group, k_in, blob, in_mask, scores, accumulate, sel, act, br, klist, list_mode, s);
 }
 
 }  // namespace prox

@@ -440,14 +440,14 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
                         for (int w4 = 0; w4 < 4; ++w4) {
                             const uint4 P = xs4[(size_t)b * nvec + vv * 4 + w4];
                             const uint32_t g8 = cgw[w4] >> 8, u8 = cuw[w4] >> 8;
-                            tge = dot2<DT>(P.x, and_or<true>(cgw[w4], 0x000F000Fu, M), tge);
-                            tue = dot2<DT>(P.x, and_or<true>(cuw[w4], 0x000F000Fu, M), tue);
-                            tgo = dot2<DT>(P.y, and_or<true>(cgw[w4] >> kOddShift, kOddMask, M), tgo);
-                            tuo = dot2<DT>(P.y, and_or<true>(cuw[w4] >> kOddShift, kOddMask, M), tuo);
-                            tge = dot2<DT>(P.z, and_or<true>(g8, 0x000F000Fu, M), tge);
-                            tue = dot2<DT>(P.z, and_or<true>(u8, 0x000F000Fu, M), tue);
-                            tgo = dot2<DT>(P.w, and_or<true>(g8 >> kOddShift, kOddMask, M), tgo);
-                            tuo = dot2<DT>(P.w, and_or<true>(u8 >> kOddShift, kOddMask, M), tuo);
+                            tge = dot2<DT>(P.x, and_or(cgw[w4], 0x000F000Fu, M), tge);
+                            tue = dot2<DT>(P.x, and_or(cuw[w4], 0x000F000Fu, M), tue);
+                            tgo = dot2<DT>(P.y, and_or(cgw[w4] >> kOddShift, kOddMask, M), tgo);
+                            tuo = dot2<DT>(P.y, and_or(cuw[w4] >> kOddShift, kOddMask, M), tuo);
+                            tge = dot2<DT>(P.z, and_or(g8, 0x000F000Fu, M), tge);
+                            tue = dot2<DT>(P.z, and_or(u8, 0x000F000Fu, M), tue);
+                            tgo = dot2<DT>(P.w, and_or(g8 >> kOddShift, kOddMask, M), tgo);
+                            tuo = dot2<DT>(P.w, and_or(u8 >> kOddShift, kOddMask, M), tuo);
                         }
                         const float2 xv = xsum[b * nv4 + vv];
                         const float ge = tge - kBiasE * xv.x, go = tgo - kBiasO * xv.y;
@@ -702,10 +702,10 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
                     const float sc = t < n ? f16_bits_to_float(R.sb[u]) : 0.0f;
                     const int tc = min(t, n - 1);
                     const uint32_t w8 = R.cw[u] >> 8;
-                    const uint32_t h[4] = {and_or<true>(R.cw[u], 0x000F000Fu, M16),
-                                           and_or<true>(R.cw[u], 0x00F000F0u, M16),
-                                           and_or<true>(w8, 0x000F000Fu, M16),
-                                           and_or<true>(w8, 0x00F000F0u, M16)};
+                    const uint32_t h[4] = {and_or(R.cw[u], 0x000F000Fu, M16),
+                                           and_or(R.cw[u], 0x00F000F0u, M16),
+                                           and_or(w8, 0x000F000Fu, M16),
+                                           and_or(w8, 0x00F000F0u, M16)};
 #pragma unroll
                     for (int b = 0; b < NB; ++b) {
                         const float sv = s_sh[tc * NB + b] * sc;
@@ -844,7 +844,6 @@ __global__ __launch_bounds__(kBlock) void stage2_kernel(
 // 30% kept, gate/up 4 x 23 us, now 42 (x comes from L2, one step in flight);
 // 16 rows are as before, 27 us.
 // ---------------------------------------------------------------------------
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kS2mTiles = 2;   // channel tiles per pass through the gate/up loop
 constexpr int kS2mRed = kS2mTiles * 2 * kMaxBlockWaves * kWave;   // float4 per pass and row tile
 
@@ -859,7 +858,7 @@ __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
     const uint16_t *__restrict__ x, int nb, int d, int f, Stage2Weights wt,
     const float *__restrict__ scores, int k_ff, uint8_t *__restrict__ mask,
     float *__restrict__ scores_copy, float *__restrict__ sbuf, Select sel_rule, ScoreBracket br,
-    int act, int32_t *__restrict__ klist, int klist_mode) {
+    int act, int32_t *__restrict__ klist) {
     constexpr int R = 16 * RT;
     const uint16_t *__restrict__ wg = static_cast<const uint16_t *>(wt.wg);
     const uint16_t *__restrict__ wu = static_cast<const uint16_t *>(wt.wu);
@@ -873,7 +872,8 @@ __global__ __launch_bounds__(kBlock) void stage2_mfma_kernel(
 
     int p0;
     const int n = stage2_slice<C>(scores, f, k_ff, mask, scores_copy, sel_rule, br, klist,
-                                  klist_mode, reinterpret_cast<uint32_t *>(dyn), cs, list, p0);
+                                  scores ? kListWrite : kListNone, reinterpret_cast<uint32_t *>(dyn),
+                                  cs, list, p0);
     __syncthreads();
 
     // ---- gate/up ----
@@ -1294,13 +1294,13 @@ template <int DT, int C, int RT>
 static hipError_t launch_stage2m_t(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
-                                   ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
+                                   ScoreBracket br, int act, int32_t *klist, hipStream_t st) {
     const size_t lds = stage2_mfma_lds_bytes();
     hipError_t e = allow_lds(stage2_mfma_kernel<DT, C, RT>, lds);
     if (e != hipSuccess) return e;
     stage2_mfma_kernel<DT, C, RT><<<nwg, kBlock, lds, st>>>(
         static_cast<const uint16_t *>(x), nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf,
-        sel_rule, br, act, klist, klist_mode);
+        sel_rule, br, act, klist);
     return hipGetLastError();
 }
 
@@ -1308,8 +1308,8 @@ template <int DT, int RT>
 static hipError_t launch_stage2m_c(const void *x, int nb, int d, int f, const Stage2Weights &wt,
                                    const float *scores, int k_ff, uint8_t *mask,
                                    float *scores_copy, float *sbuf, int nwg, Select sel_rule,
-                                   ScoreBracket br, int act, int32_t *klist, int klist_mode, hipStream_t st) {
-#define S2M(C_) launch_stage2m_t<DT, C_, RT>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
+                                   ScoreBracket br, int act, int32_t *klist, hipStream_t st) {
+#define S2M(C_) launch_stage2m_t<DT, C_, RT>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, st)
     if (scores && f <= 4 * kBlock) return S2M(4);
     if (scores && f <= 8 * kBlock) return S2M(8);
     if (scores && f <= 12 * kBlock) return S2M(12);
@@ -1324,15 +1324,13 @@ hipError_t launch_stage2_mfma(int dtype, const void *x, int nb, int d, int f,
                               const Stage2Weights &wt, const float *scores, int k_ff,
                               uint8_t *mask, float *scores_copy, float *sbuf, int nwg,
                               Select sel_rule, ScoreBracket br, int act, int32_t *klist,
-                              int klist_mode, hipStream_t st) {
+                              hipStream_t st) {
     const int n_ch = scores && !sel_rule.tau_mode ? k_ff : f;   // the kept-list length
     if (nb < 1 || nb > kStage2MfmaMaxRows || !stage2_mfma_ok(d, wt.wq) || nwg < 1 ||
         nwg > kStage2MaxWGs || (long long)n_ch > (long long)kMaxSlice * nwg || !sbuf)
         return hipErrorInvalidValue;
-    // The down launch reads the kept list: a sparse call writes or reads it.
-    if ((scores != nullptr) != (klist_mode != kListNone) || (scores && !klist))
-        return hipErrorInvalidValue;
-#define S2M(DT_, RT_) return launch_stage2m_c<DT_, RT_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, klist_mode, st)
+    if (scores && !klist) return hipErrorInvalidValue;   // the down launch reads the kept list
+#define S2M(DT_, RT_) return launch_stage2m_c<DT_, RT_>(x, nb, d, f, wt, scores, k_ff, mask, scores_copy, sbuf, nwg, sel_rule, br, act, klist, st)
     const int rt = stage2_row_tiles(nb);
     if (dtype == kBF16) {
         if (rt == 1) S2M(kBF16, 1);

@@ -2,7 +2,6 @@
 // host, workspace carving, and the launch sequence of each entry point.
 #include <prox.h>
 
-#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -177,17 +176,22 @@ int stage1_mfma_rows(int d, int qbits, int group, int batch, int k_in) {
 // The bracket of a top-k call's channel selection (ScoreBracket).  Its order
 // statistics go to the end of the kept-list area, [f - 2 n, f), which a call
 // that keeps k_ff <= f - 2 n channels never writes: the list takes [0, k_ff) and
-// f, and in a call without a list nothing.  NULL stats when there is no room,
-// d_ff is at most 4096 (with four scores per thread the radix passes are as
-// quick, and Stage 1 is spared its part: 23.2 against 23.9 us for the 1024 x
-// 3072 call), or k_ff is 0 (threshold mode).
+// f, and in a call without a list nothing.  NULL stats when d_ff is at most 4096
+// (with four scores per thread the radix passes are as quick, and Stage 1 is
+// spared its part: 23.2 against 23.9 us for the 1024 x 3072 call), when less than
+// a sixteenth or more than seven eighths of the channels are kept (the bracket
+// mostly misses there, and its counting pass is lost: 8192 x 28672 with 1% kept
+// 51.9 us without it, 56.1 with; 95%: 246.8 and 250.9), so also when k_ff is 0
+// (threshold mode).
 ScoreBracket score_bracket(int f, int k_ff, int32_t *klist) {
     ScoreBracket br{};
     const int T = proxy_tile(f), n = f / T;
-    if (k_ff < 1 || f <= 4 * kBlock || k_ff > f - 2 * n - 2) return br;
+    if (f <= 4 * kBlock || 16 * k_ff < f || 8 * k_ff > 7 * f) return br;
+    // The kept share is at least 4 ranks from either end of a tile, and f - 2 n
+    // (31/32 of f or more) leaves room for the list.
     const double at = (double)k_ff * (T + 1) / (f + 1);   // expected rank in a tile, from 1
     const int reach = T / 64;
-    br.r1 = std::min(std::max((int)at - reach, 1), T - 2 * reach - 1);
+    br.r1 = (int)at - reach;
     br.r2 = br.r1 + 2 * reach + 1;
     const double half = 0.35 + 4 * 0.17 * T / std::sqrt((double)f);   // ranks
     br.at = (float)((at - br.r1) / (br.r2 - br.r1));

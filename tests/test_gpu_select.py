@@ -38,7 +38,8 @@ def test_mask_is_the_top_k_of_the_scores(f, batch, kind):
     p = prox.pack_proxy(w, prox.INT4, 128)
     x = prox.from_bits(W.to_bits(rng.laplace(size=(batch, D)).astype(np.float32), W.DT_BF16), W.DT_BF16)
     scores = torch.empty(f, dtype=torch.float32, device="cuda")
-    for k in sorted({1, 2, f // 50, int(0.3 * f), f // 2, int(0.96 * f), f - 1, f}):
+    for k in sorted({1, 2, f // 50, f // 16, f // 16 + 1, int(0.3 * f), f // 2, 7 * f // 8, 7 * f // 8 + 1,
+                     int(0.96 * f), f - 1, f}):
         print(f"[select] {kind} f={f} B={batch} k={k}", flush=True)
         _, mask = prox.ffn_sparse(w, p, x, D // 2, k, scores=scores)
         torch.cuda.synchronize()

@@ -157,10 +157,17 @@ prox_status stage2_and_reduce(const Model &m, const void *x, int batch, int k_ff
 // the small-batch kernel (4096 x 14336, four rows: the call takes 54 us, 57 on the
 // 16-row matrix-core kernel); up to 16 rows at d <= 4096 on that kernel (16 rows:
 // one launch of 23 us, where the batch kernels' three take 31); the rest on the
-// batch kernels, which select once for all rows (the call at 8192 x 14336: 12 rows 94.5
-// us, 129.8 in two launches of 8 rows; 6 rows 110.6, 113.5 in one).  The same for
-// both selection rules, so that equal sets give equal bits.  INT8 and unquantised
-// proxies: the dot-product kernel.
+// batch kernels, which select once for all rows.  Calls in us, in brackets with
+// launches of 16 rows (8 above d = 4096) or, for the last line, of one row on a
+// dot-product kernel (and, worth about 1 us, without the score bracket):
+//   17, 64 rows   512 x 2048: 46.8, 86.6 (56.6, 121.5); 2048 x 8192: 75.9, 178.4
+//                 (89.6, 219.1)
+//   5, 8 rows     8192 x 28672: 151.1, 171.4 (169.2, 194.1); 8192 x 1024: 61.3, 70.1
+//                 (63.6, 70.4); 4224 x 512: 48.6, 52.5 (47.6, 51.2)
+//   2, 4 rows     8320 x 28672: 139.5, 159.0 (167.5, 268.6); 16384 x 320: 68.5, 83.0
+//                 (95.3, 179.2)
+// The same for both selection rules, so that equal sets give equal bits.  INT8 and
+// unquantised proxies: the dot-product kernel.
 enum Stage1Route { kStage1Dot, kStage1Small, kStage1Mfma, kStage1Batch };
 Stage1Route stage1_route(int d, int qbits, int batch) {
     if (qbits != 4) return kStage1Dot;

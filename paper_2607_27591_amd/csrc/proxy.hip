@@ -16,7 +16,7 @@
 // bias (128 times sum(x)) is subtracted and the group's scale applied once per
 // group, column and lane group.  Lane groups and waves are summed in a fixed
 // order, so results are deterministic.  Up to 4 batch rows per launch; INT4
-// proxies have kernels of their own (proxy_small_kernel, proxy_mfma_kernel).
+// proxies have kernels of their own (proxy_small.hip, proxy_mfma.hip, proxy_batch.hip).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"

@@ -14,10 +14,10 @@
 //          order) the A operand, as in proxy_small_kernel but with 16 batch rows per
 //          tile.
 // The results meet in LDS in wave order.  At 4096 x 14336 and 64 rows keys, gather
-// and stream take 3, 8 and 33 us (the stream issues the dequantisation once per row
+// and stream take 3, 8 and 34 us (the stream issues the dequantisation once per row
 // tile and window), against 4 x 27 us in launches of 16 rows, each listing again;
-// the call 108 us, from 178 (111 with bf16 operands, which take 36 instructions to
-// unpack a quad where fp16 takes 32).
+// the call 110 us, from 178 (108 with x scaled into fp16, which takes 32 instructions
+// to unpack a quad where bf16 takes 36, but ties the rows' ranges together).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "topk.hpp"

@@ -1,8 +1,8 @@
-// Stage 1 of the sparse decode step for several batch rows at once, on the
-// matrix cores (Sec. 4.1 Stage 1 with the INT4 proxy of Sec. 3.2 / 4.3).  It
-// computes the proxy and the score as proxy.hip states them for up to 16 rows per
-// launch (5 to 16 rows at d_model up to 4096), so the proxy codes of a kept input
-// row are read once for all of them.
+// Stage 1 of the sparse decode step for 5 to 16 batch rows at d_model up to 4096,
+// on the matrix cores (Sec. 4.1 Stage 1 with the INT4 proxy of Sec. 3.2 / 4.3).  It
+// computes the proxy and the score as proxy.hip states them, all rows in one launch
+// (8 where the list is too long for 16), so the proxy codes of a kept input row are
+// read once for all of them.
 //
 // The proxy GEMV of a column tile is a product of x (batch rows x kept input
 // rows) with the dequantised codes (kept input rows x columns), done as

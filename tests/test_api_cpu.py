@@ -105,7 +105,8 @@ def test_sizes():
     assert prox.workspace_bytes(4096, 12288, 64) > prox.workspace_bytes(4096, 12288, 16)
     # Partial y sized by path: up to 8 rows both weight kinds take one row set
     # per Stage 2 workgroup; past 8 rows at d_model >= 4096 the 16-bit path
-    # keeps 64 groups (plus s), INT4 weights still 256 workgroups.
+    # keeps 16 groups or fewer (plus s; the size stays that of 8 rows), INT4
+    # weights still 256 workgroups.
     for B in (1, 4, 8):
         assert prox.workspace_bytes(8192, 28672, B) == prox.workspace_bytes(8192, 28672, B, w4=True)
     assert prox.workspace_bytes(4096, 14336, 16) < prox.workspace_bytes(4096, 14336, 16, w4=True)
@@ -155,7 +156,7 @@ def test_stage1_kernel_selection():
 
 def test_stage2_kernel_selection():
     # More than eight batch rows of 16-bit weights with d_model >= 4096 take
-    # the matrix-core Stage 2 (16 rows per launch); otherwise the VALU kernel
+    # the matrix-core Stage 2 (tiles of 16 rows); otherwise the VALU kernel
     # (8 rows per launch, fewer for INT4 weights at wide d_model).
     rows = prox.stage2_rows
     assert rows(4096, 14336, False, 16) == 16

@@ -28,45 +28,43 @@ SMALL = {
     "bf16_i8_g128_640x513_b3": W.small_config(d=640, f=513, batch=3, seed=8, qbits=8),
     "bf16_i4_2048x3000_b4": W.small_config(d=2048, f=3000, batch=4, seed=9, in_frac=0.4,
                                            sigma_w=0.02),
-    # Five or more rows run on the matrix-core proxy: fp16 codes, and a 4096-wide
-    # input whose threshold-mode list allows only 8 rows per launch (two
-    # launches, the second accumulating into the scores).
+    # 5 to 16 rows up to d_model 4096 run on the 16-row matrix-core proxy: fp16
+    # codes, and a 4096-wide input whose threshold-mode list allows only 8 rows
+    # per launch (two launches, the second accumulating into the scores).
     "f16_i4_768x900_b7": W.small_config(d=768, f=900, batch=7, seed=13, dtype=W.DT_F16),
     "bf16_i4_4096x1500_b12": W.small_config(d=4096, f=1500, batch=12, seed=14, in_frac=0.7,
                                             sigma_w=0.02),
-    # Batches past one launch's rows: 40 rows on the matrix cores (16 + 16 + 8
-    # per Stage 1 launch, five 8-row Stage 2 launches), and 20 INT8 rows on the
-    # dot-product kernel (five 4-row Stage 1 launches).
+    # Batches past one launch's rows: 40 rows on the batch Stage 1 (four row
+    # tiles; five 8-row Stage 2 launches), and 20 INT8 rows on the dot-product
+    # kernel (five 4-row Stage 1 launches).
     "bf16_i4_1024x1600_b40": W.small_config(d=1024, f=1600, batch=40, seed=16, in_frac=0.4,
                                             sigma_w=0.02),
     "f16_i8_512x700_b20": W.small_config(d=512, f=700, batch=20, seed=17, dtype=W.DT_F16,
                                          qbits=8, group=512, ff_frac=0.5),
-    # d_model 16384 on the matrix cores: 16 input rows per thread, 8 batch
-    # rows per launch.
+    # d_model 16384 on the batch Stage 1: 16 inputs per thread in its selection.
     "bf16_i4_16384x320_b6": W.small_config(d=16384, f=320, batch=6, seed=15, in_frac=0.3,
                                            sigma_w=0.01),
     # More than eight rows of 16-bit weights at d_model >= 4096 run Stage 2 on
-    # the matrix cores: 9 fp16 rows in one chunk, and 33 rows as chunks of 16,
-    # 16 and 1 sharing one kept list.
+    # the matrix cores: 9 fp16 rows in one row tile, and 33 rows in four.
     "f16_i4_4096x1000_b9": W.small_config(d=4096, f=1000, batch=9, seed=18, dtype=W.DT_F16,
                                           in_frac=0.5, sigma_w=0.02),
     "bf16_i4_8192x700_b33": W.small_config(d=8192, f=700, batch=33, seed=19, in_frac=0.4,
                                            sigma_w=0.01),
     # The paper's per-row INT4 proxy (one scale per output channel, group =
-    # d_model): batch 1 on the dot-product Stage 1, batch 6 on the matrix cores.
+    # d_model): batch 1 on the small-batch Stage 1, batch 6 on the 16-row one.
     "bf16_i4_perrow_1024x1600_b1": W.small_config(d=1024, f=1600, batch=1, seed=21, group=1024,
                                                   in_frac=0.4, sigma_w=0.02, n_outliers=8),
     "bf16_i4_perrow_2048x1200_b6": W.small_config(d=2048, f=1200, batch=6, seed=22, group=2048,
                                                   in_frac=0.4, sigma_w=0.02),
-    # Maximum sizes: d_model 16384 (16 input rows per thread, 1 batch row
-    # per proxy launch) and d_ff 65536 (64 score rows per thread).
+    # Maximum sizes: d_model 16384 (three rows on the batch Stage 1) and d_ff
+    # 65536 (64 score rows per thread).
     "bf16_i4_16384x320_b3": W.small_config(d=16384, f=320, batch=3, seed=10, in_frac=0.3,
                                            sigma_w=0.01),
     "f16_i4_128x65536_b2": W.small_config(d=128, f=65536, batch=2, seed=12, dtype=W.DT_F16,
                                           ff_frac=0.2),
-    # The largest batch a call takes (64 rows): four 16-row launches of each
-    # matrix-core stage, and sixteen 4-row Stage 1 plus eight 8-row Stage 2
-    # launches of the dot-product kernels.
+    # The largest batch a call takes (64 rows): four row tiles of the batch
+    # Stage 1 and the matrix-core Stage 2, and sixteen 4-row Stage 1 plus eight
+    # 8-row Stage 2 launches of the dot-product kernels.
     "bf16_i4_4096x1000_b64": W.small_config(d=4096, f=1000, batch=64, seed=24, in_frac=0.4,
                                             sigma_w=0.02),
     "f16_i8_512x700_b64": W.small_config(d=512, f=700, batch=64, seed=25, dtype=W.DT_F16,
